@@ -45,15 +45,20 @@ enum { ERR_DRY = 1, ERR_NONFINITE = 2 };
 
 // Device scalars of a context.
 struct DevScal {
-  unsigned long long a_n[2];     // alpha of U^n (bits of positive doubles)
-  unsigned long long a_1[2];     // alpha of U^(1)
-  unsigned long long a_2[2];     // alpha of U^(2)
-  unsigned long long a_next[2];  // alpha of U^(n+1)
-  unsigned long long a_fix[2];   // fixed alpha
-  unsigned long long a_rhs[2];   // alpha used by a bare right-hand side
   double dt, t, t_end, pad0;
   int active, steps, err, pad1;
 };
+
+// A set of Lax-Friedrichs speeds: (alpha_x, alpha_y) (bits of positive doubles) in each of
+// a power-of-two number of slots, one 128-byte line per slot; the set's value is the maximum over
+// its slots. Atomics on one address are served one after another, 8.6 ns apart on this device when they come
+// from all XCDs: with a single slot the wavefronts that end together queue there (k_alpha
+// over 1021 x 777 nodes took 284 us for 25 MB). Spread over 64 lines the same reduction is bound by its
+// reads again. A reader loads one slot per lane and takes the maximum over the wavefront.
+constexpr int ASTRIDE = 16;  // 64-bit words per slot
+constexpr int ASLOTS = 64;   // slots of a context's sets
+constexpr int ASET = ASLOTS * ASTRIDE;
+enum { SP_N = 0, SP_1, SP_2, SP_NEXT, SP_FIX, SP_RHS, SP_SETS };  // alpha of U^n, U^(1), U^(2), U^(n+1), fixed, bare RHS
 
 template <class T>
 struct KArgs {
@@ -68,6 +73,7 @@ struct KArgs {
   const unsigned long long* a_in;  // Lax-Friedrichs speeds used
   unsigned long long* a_out;       // max-reduction of the output state's speeds
   DevScal* sc;
+  int amask;                       // slots of the sets of speeds, less one
   int nx, ny, bcx, bcy, limiter, rows;
   T dx, dy, idx, idy, g, eps;
 };
@@ -246,16 +252,36 @@ __device__ __forceinline__ void speeds(T e, T m, T w, T b, T g, T& ax, T& ay,
   ay = fmax(ay, sy);
 }
 
+// The two speeds of a set (all 64 lanes of a wavefront take part), in scalar registers. A grid of few
+// wavefronts keeps one slot, which needs no reduction.
+__device__ __forceinline__ double uniform(double v) {
+  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)u);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(u >> 32));
+  return bits2d(((unsigned long long)hi << 32) | lo);
+}
+__device__ __forceinline__ void read_speeds(const unsigned long long* __restrict__ p, int amask, double& ax, double& ay) {
+  if (amask == 0) {
+    ax = bits2d(p[0]);
+    ay = bits2d(p[1]);
+    return;
+  }
+  const unsigned long long* q = p + (size_t)((int)(threadIdx.x & (WAVE - 1)) & amask) * ASTRIDE;
+  ax = uniform(wave_max(bits2d(q[0])));
+  ay = uniform(wave_max(bits2d(q[1])));
+}
+
 template <class T>
-__device__ __forceinline__ void flush_speeds(const KArgs<T>& a, T ax, T ay, int err) {
+__device__ __forceinline__ void flush_speeds(const KArgs<T>& a, int slot, T ax, T ay, int err) {
   ax = wave_max(ax);
   ay = wave_max(ay);
   int e = err;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) e |= __shfl_xor(e, o, WAVE);
   if (threadIdx.x == 0) {
-    atomicMax(&a.a_out[0], (unsigned long long)__double_as_longlong((double)ax));
-    atomicMax(&a.a_out[1], (unsigned long long)__double_as_longlong((double)ay));
+    unsigned long long* o = a.a_out + (size_t)(slot & a.amask) * ASTRIDE;
+    atomicMax(&o[0], (unsigned long long)__double_as_longlong((double)ax));
+    atomicMax(&o[1], (unsigned long long)__double_as_longlong((double)ay));
     if (e) atomicOr(&a.sc->err, e);
   }
 }
@@ -275,7 +301,9 @@ __device__ __forceinline__ void stage_tile(const KArgs<T>& a, int tx, int ty) {
   const int r1 = DIM == 2 ? min(r0 + a.rows, a.ny) : 1;
   const bool col_out = lane >= 2 && lane < WAVE - 2 && c < a.nx;
   const int cq = col_out ? c : 0;  // a column that is always inside the grid
-  const T axl = T(bits2d(a.a_in[0])), ayl = T(bits2d(a.a_in[1]));
+  double sax, say;
+  read_speeds(a.a_in, a.amask, sax, say);
+  const T axl = T(sax), ayl = T(say);
   const size_t n = (size_t)a.nx * (DIM == 2 ? a.ny : 1);
   const T dt = MODE == MODE_RHS ? T(0.0) : T(a.sc->dt);
   const int nu = DIM == 2 ? 3 : 2, nd = DIM == 2 ? 6 : 2;
@@ -470,7 +498,7 @@ __device__ __forceinline__ void stage_tile(const KArgs<T>& a, int tx, int ty) {
     }
   }
   if (MODE != MODE_RHS) {
-    flush_speeds(a, amx, amy, err);
+    flush_speeds(a, tx + ty, amx, amy, err);
   } else {
     int e = err;
 #pragma unroll
@@ -498,28 +526,52 @@ __global__ __launch_bounds__(WAVE) void k_stage(KArgs<T> a) {
 }
 
 // --------------------------------------------------------------------------- small kernels
-// Lax-Friedrichs speeds of a state (grid-stride), max-reduced into out[2].
-template <class T, int DIM>
-__global__ __launch_bounds__(256) void k_alpha(const T* __restrict__ S, const T* __restrict__ b, size_t n,
-                                               T g, unsigned long long* out, int* errp) {
-  T ax = T(0.0), ay = T(0.0);
-  int err = 0;
-  for (size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x; q < n; q += (size_t)gridDim.x * blockDim.x)
-    speeds(S[q], S[n + q], DIM == 2 ? S[2 * n + q] : T(0.0), b[q], g, ax, ay, err);
+// Largest speeds of a workgroup of 256 threads into slot blockIdx.x of a set.
+template <class T>
+__device__ __forceinline__ void block_speeds(T ax, T ay, int err, unsigned long long* out, int amask, int* errp) {
+  __shared__ double sx[4], sy[4];
+  __shared__ int se[4];
   ax = wave_max(ax);
   ay = wave_max(ay);
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) err |= __shfl_xor(err, o, WAVE);
   if ((threadIdx.x & (WAVE - 1)) == 0) {
-    atomicMax(&out[0], (unsigned long long)__double_as_longlong((double)ax));
-    atomicMax(&out[1], (unsigned long long)__double_as_longlong((double)ay));
-    if (err) atomicOr(errp, err);
+    const int w = (int)(threadIdx.x / WAVE);
+    sx[w] = (double)ax; sy[w] = (double)ay; se[w] = err;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const double mx = fmax(fmax(sx[0], sx[1]), fmax(sx[2], sx[3])), my = fmax(fmax(sy[0], sy[1]), fmax(sy[2], sy[3]));
+    const int e = (se[0] | se[1]) | (se[2] | se[3]);
+    unsigned long long* o = out + (size_t)((int)blockIdx.x & amask) * ASTRIDE;
+    atomicMax(&o[0], (unsigned long long)__double_as_longlong(mx));
+    atomicMax(&o[1], (unsigned long long)__double_as_longlong(my));
+    if (e) atomicOr(errp, e);
   }
 }
 
-// Set two alpha slots (zero, or given values).
+// Lax-Friedrichs speeds of a state (grid-stride), max-reduced into a set. Bound by its reads (b and the
+// first three planes).
+template <class T, int DIM>
+__global__ __launch_bounds__(256) void k_alpha(const T* __restrict__ S, const T* __restrict__ b, size_t n,
+                                               T g, unsigned long long* out, int amask, int* errp) {
+  T ax = T(0.0), ay = T(0.0);
+  int err = 0;
+  for (size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x; q < n; q += (size_t)gridDim.x * blockDim.x)
+    speeds(S[q], S[n + q], DIM == 2 ? S[2 * n + q] : T(0.0), b[q], g, ax, ay, err);
+  block_speeds(ax, ay, err, out, amask, errp);
+}
+
+// Set a pair of words.
 __global__ void k_set2(unsigned long long* p, unsigned long long v0, unsigned long long v1) {
   if (threadIdx.x == 0) { p[0] = v0; p[1] = v1; }
+}
+
+// Set a set of ASLOTS speeds to given values (one wavefront).
+__global__ void k_set_speeds(unsigned long long* p, unsigned long long v0, unsigned long long v1) {
+  unsigned long long* q = p + (size_t)threadIdx.x * ASTRIDE;
+  q[0] = threadIdx.x == 0 ? v0 : 0ull;
+  q[1] = threadIdx.x == 0 ? v1 : 0ull;
 }
 
 // Reset the clock of a run or a single step (the error flag is left alone).
@@ -547,25 +599,37 @@ constexpr size_t NOALLOC_BYTES = size_t(32) << 20;
 constexpr size_t NOALLOC_SCAL = 256;  // DevScal at the start, stage planes after it
 static_assert(sizeof(DevScal) <= NOALLOC_SCAL, "device scalars must fit their slot");
 static __device__ __align__(256) unsigned char scratch[NOALLOC_BYTES];
+static __device__ __align__(256) unsigned long long scratch_speeds[SP_SETS * ASET];
 
 // Start of an allocation-free step: the fixed speeds and a cleared error flag (the array keeps
-// whatever the previous call on this GPU left).
-__global__ void k_noalloc_setup(DevScal* s, unsigned long long afx, unsigned long long afy) {
-  if (threadIdx.x == 0) {
-    s->a_fix[0] = afx;
-    s->a_fix[1] = afy;
-    s->err = 0;
-  }
+// whatever the previous call on this GPU left). One wavefront.
+__global__ void k_noalloc_setup(DevScal* s, unsigned long long* sp, unsigned long long afx, unsigned long long afy) {
+  unsigned long long* q = sp + SP_FIX * ASET + (size_t)threadIdx.x * ASTRIDE;
+  q[0] = threadIdx.x == 0 ? afx : 0ull;
+  q[1] = threadIdx.x == 0 ? afy : 0ull;
+  if (threadIdx.x == 0) s->err = 0;
 }
 
 // Start of a step: alpha of U^n from the previous step's reduction, the CFL step (or fixed),
-// clipped at t_end; clears the reductions this step fills.
-__global__ void k_prologue(DevScal* s, int dim, int fixed_dt, double fdt, double cfl, double dx, double dy,
-                           int use_tend) {
-  if (threadIdx.x != 0) return;
-  s->a_n[0] = s->a_next[0];
-  s->a_n[1] = s->a_next[1];
-  const double ax = bits2d(s->a_n[0]), ay = bits2d(s->a_n[1]);
+// clipped at t_end; clears the reductions this step fills. One wavefront, a lane per slot in use.
+__global__ void k_prologue(DevScal* s, unsigned long long* sp, int amask, int dim, int fixed_dt, double fdt, double cfl, double dx,
+                           double dy, int use_tend) {
+  const int l = (int)threadIdx.x;
+  if (l > amask) return;
+  unsigned long long* nx = sp + SP_NEXT * ASET + l * ASTRIDE;
+  const unsigned long long u0 = nx[0], u1 = nx[1];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    unsigned long long* q = sp + (k == 0 ? SP_N : (k == 1 ? SP_1 : (k == 2 ? SP_2 : SP_NEXT))) * ASET + l * ASTRIDE;
+    q[0] = k == 0 ? u0 : 0ull;
+    q[1] = k == 0 ? u1 : 0ull;
+  }
+  double ax = bits2d(u0), ay = bits2d(u1);
+  if (amask != 0) {
+    ax = wave_max(ax);
+    ay = wave_max(ay);
+  }
+  if (l != 0) return;
   double dt = fixed_dt ? fdt : cfl_step(dim, cfl, ax, ay, dx, dy);
   int active = 1;
   if (use_tend) {
@@ -579,9 +643,6 @@ __global__ void k_prologue(DevScal* s, int dim, int fixed_dt, double fdt, double
   s->active = active;
   s->dt = dt;
   if (active) { s->t += dt; s->steps += 1; }
-  s->a_1[0] = s->a_1[1] = 0ull;
-  s->a_2[0] = s->a_2[1] = 0ull;
-  s->a_next[0] = s->a_next[1] = 0ull;
 }
 
 // Stand-alone limiter: one thread per node, neighbours read directly.
@@ -628,6 +689,7 @@ struct swe_hweno_ctx {
   void *b = nullptr, *bx = nullptr, *by = nullptr;  // planes of the context's type
   void *S1 = nullptr, *S2 = nullptr, *Dn = nullptr;
   DevScal* sc = nullptr;
+  unsigned long long* sp = nullptr;  // SP_SETS sets of speeds
   hipGraphExec_t g1 = nullptr, g8 = nullptr;
   const void* g_state = nullptr;
   int g_tend = 0;
@@ -681,11 +743,25 @@ unsigned long long dbits(double v) {
 
 template <class T> bool is_type(const swe_hweno_ctx* c) { return c->f32 == (sizeof(T) == sizeof(float) ? 1 : 0); }
 
+dim3 stage_grid(const swe_hweno_ctx* c) {
+  const unsigned gx = (unsigned)((c->p.nx + OUT_COLS - 1) / OUT_COLS);
+  const unsigned gy = c->p.dim == 2 ? (unsigned)((c->p.ny + c->rows - 1) / c->rows) : 1u;
+  return dim3(gx, gy, 1);
+}
+
+// Slots in use, less one: one slot up to 48 wavefronts in a stage (their atomics queue for under 1 us, about
+// what reading and reducing 64 slots costs each of a step's kernels), else all.
+int speeds_mask(const swe_hweno_ctx* c) {
+  const dim3 g = stage_grid(c);
+  return g.x * g.y <= 48 ? 0 : ASLOTS - 1;
+}
+
 template <class T> KArgs<T> base_args(const swe_hweno_ctx* c) {
   KArgs<T> a;
   std::memset(&a, 0, sizeof a);
   a.b = (const T*)c->b; a.bx = (const T*)c->bx; a.by = (const T*)c->by;
   a.sc = c->sc;
+  a.amask = speeds_mask(c);
   a.nx = c->p.nx; a.ny = c->p.dim == 2 ? c->p.ny : 1;
   a.bcx = c->p.bc_x; a.bcy = c->p.bc_y;
   a.limiter = (c->p.flags & SWE_NO_LIMITER) ? 0 : 1;
@@ -698,25 +774,25 @@ template <class T> KArgs<T> base_args(const swe_hweno_ctx* c) {
   return a;
 }
 
-dim3 stage_grid(const swe_hweno_ctx* c) {
-  const unsigned gx = (unsigned)((c->p.nx + OUT_COLS - 1) / OUT_COLS);
-  const unsigned gy = c->p.dim == 2 ? (unsigned)((c->p.ny + c->rows - 1) / c->rows) : 1u;
-  return dim3(gx, gy, 1);
-}
-
 template <class T, int MODE> void launch_stage_mode(const swe_hweno_ctx* c, const KArgs<T>& a, hipStream_t s) {
   if (c->p.dim == 2) hipLaunchKernelGGL((k_stage<T, 2, MODE>), stage_grid(c), dim3(WAVE), 0, s, a);
   else hipLaunchKernelGGL((k_stage<T, 1, MODE>), stage_grid(c), dim3(WAVE), 0, s, a);
 }
 
-template <class T> void launch_alpha(const swe_hweno_ctx* c, const T* S, unsigned long long* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_set2, dim3(1), dim3(64), 0, s, out, 0ull, 0ull);
+unsigned long long* speeds_set(const swe_hweno_ctx* c, int set) { return c->sp + (size_t)set * ASET; }
+
+template <class T> void launch_alpha(const swe_hweno_ctx* c, const T* S, int set, hipStream_t s) {
+  unsigned long long* out = speeds_set(c, set);
+  hipLaunchKernelGGL(k_set_speeds, dim3(1), dim3(ASLOTS), 0, s, out, 0ull, 0ull);
+  // a node per thread up to eight workgroups per CU, which fill the memory system; each ends in one pair of atomics
   const size_t blocks = (c->n + 255) / 256;
-  const unsigned grid = (unsigned)(blocks < 4096 ? blocks : 4096);
+  const unsigned grid = (unsigned)(blocks < 2048 ? blocks : 2048);
   if (c->p.dim == 2)
-    hipLaunchKernelGGL((k_alpha<T, 2>), dim3(grid), dim3(256), 0, s, S, (const T*)c->b, c->n, T(c->p.g), out, &c->sc->err);
+    hipLaunchKernelGGL((k_alpha<T, 2>), dim3(grid), dim3(256), 0, s, S, (const T*)c->b, c->n, T(c->p.g), out, speeds_mask(c),
+                       &c->sc->err);
   else
-    hipLaunchKernelGGL((k_alpha<T, 1>), dim3(grid), dim3(256), 0, s, S, (const T*)c->b, c->n, T(c->p.g), out, &c->sc->err);
+    hipLaunchKernelGGL((k_alpha<T, 1>), dim3(grid), dim3(256), 0, s, S, (const T*)c->b, c->n, T(c->p.g), out, speeds_mask(c),
+                       &c->sc->err);
 }
 
 hipEvent_t take_event(swe_hweno_ctx* c) {
@@ -766,26 +842,26 @@ template <class T> void enqueue_step(swe_hweno_ctx* c, T* state, int use_tend, h
   const bool fa = (c->p.flags & SWE_FIXED_ALPHA) != 0;
   const double dx = (c->p.x1 - c->p.x0) / c->p.nx;
   const double dy = c->p.dim == 2 ? (c->p.y1 - c->p.y0) / c->p.ny : 1.0;
-  hipLaunchKernelGGL(k_prologue, dim3(1), dim3(64), 0, s, c->sc, c->p.dim, (c->p.flags & SWE_FIXED_DT) ? 1 : 0,
+  hipLaunchKernelGGL(k_prologue, dim3(1), dim3(ASLOTS), 0, s, c->sc, c->sp, speeds_mask(c), c->p.dim, (c->p.flags & SWE_FIXED_DT) ? 1 : 0,
                      c->p.fixed_dt, c->p.cfl, dx, dy, use_tend);
   T* S1 = (T*)c->S1;
   T* S2 = (T*)c->S2;
   T* Dn = (T*)c->Dn;
   KArgs<T> a = base;
   a.S = state; a.out = S1; a.Dn_out = Dn;
-  a.a_in = fa ? c->sc->a_fix : c->sc->a_n; a.a_out = c->sc->a_1;
+  a.a_in = speeds_set(c, fa ? SP_FIX : SP_N); a.a_out = speeds_set(c, SP_1);
   int id = time_begin(c, s);
   launch_stage_mode<T, MODE_STAGE0>(c, a, s);
   time_end(c, id, 1, s);
   a = base;
   a.S = S1; a.Sn = state; a.Dn = Dn; a.out = S2;
-  a.a_in = fa ? c->sc->a_fix : c->sc->a_1; a.a_out = c->sc->a_2;
+  a.a_in = speeds_set(c, fa ? SP_FIX : SP_1); a.a_out = speeds_set(c, SP_2);
   id = time_begin(c, s);
   launch_stage_mode<T, MODE_STAGE1>(c, a, s);
   time_end(c, id, 2, s);
   a = base;
   a.S = S2; a.Sn = state; a.Dn = Dn; a.out = state;
-  a.a_in = fa ? c->sc->a_fix : c->sc->a_2; a.a_out = c->sc->a_next;
+  a.a_in = speeds_set(c, fa ? SP_FIX : SP_2); a.a_out = speeds_set(c, SP_NEXT);
   id = time_begin(c, s);
   launch_stage_mode<T, MODE_STAGE2>(c, a, s);
   time_end(c, id, 3, s);
@@ -868,6 +944,7 @@ int init_impl(const swe_hweno_params* p, const T* b, const T* bx, const T* by, v
   ok = ok && hipMalloc(&c->S2, plane * c->nf) == hipSuccess;
   ok = ok && hipMalloc(&c->Dn, plane * c->nd) == hipSuccess;
   ok = ok && hipMalloc(&c->sc, sizeof(DevScal)) == hipSuccess;
+  ok = ok && hipMalloc(&c->sp, sizeof(unsigned long long) * SP_SETS * ASET) == hipSuccess;
   if (!ok) { swe_hweno_destroy(c); return SWE_ENOMEM; }
   c->bx = (T*)c->b + c->n;
   c->by = (T*)c->b + 2 * c->n;
@@ -885,8 +962,9 @@ int init_impl(const swe_hweno_params* p, const T* b, const T* bx, const T* by, v
   else ok = ok && hipMemsetAsync(c->by, 0, plane, c->stream) == hipSuccess;
   DevScal init;
   std::memset(&init, 0, sizeof init);
-  init.a_fix[0] = dbits(p->alpha_x);
-  init.a_fix[1] = dbits(p->dim == 2 ? p->alpha_y : 0.0);
+  hipLaunchKernelGGL(k_set_speeds, dim3(1), dim3(ASLOTS), 0, c->stream, speeds_set(c, SP_FIX), dbits(p->alpha_x),
+                     dbits(p->dim == 2 ? p->alpha_y : 0.0));
+  ok = ok && hipGetLastError() == hipSuccess;
   ok = ok && hipMemcpyAsync(c->sc, &init, sizeof init, hipMemcpyHostToDevice, c->stream) == hipSuccess;
   ok = ok && hipStreamSynchronize(c->stream) == hipSuccess;
   if (!ok) { swe_hweno_destroy(c); return SWE_EHIP; }
@@ -902,12 +980,12 @@ template <class T> int rhs_impl(swe_hweno_ctx* c, const T* state, T* rhs, double
   if (alpha_x > 0 && c->p.dim == 2 && !(alpha_y > 0 && std::isfinite(alpha_y))) return SWE_EINVAL;
   const size_t bytes = c->n * c->nf * sizeof(T);
   if ((const char*)rhs < (const char*)state + bytes && (const char*)state < (const char*)rhs + bytes) return SWE_EINVAL;
-  if (alpha_x < 0) launch_alpha<T>(c, state, c->sc->a_rhs, c->stream);
+  if (alpha_x < 0) launch_alpha<T>(c, state, SP_RHS, c->stream);
   else
-    hipLaunchKernelGGL(k_set2, dim3(1), dim3(64), 0, c->stream, c->sc->a_rhs, dbits(alpha_x),
+    hipLaunchKernelGGL(k_set_speeds, dim3(1), dim3(ASLOTS), 0, c->stream, speeds_set(c, SP_RHS), dbits(alpha_x),
                        dbits(c->p.dim == 2 ? alpha_y : 0.0));
   KArgs<T> a = base_args<T>(c);
-  a.S = state; a.out = rhs; a.a_in = c->sc->a_rhs;
+  a.S = state; a.out = rhs; a.a_in = speeds_set(c, SP_RHS);
   const int id = time_begin(c, c->stream);
   launch_stage_mode<T, MODE_RHS>(c, a, c->stream);
   time_end(c, id, 0, c->stream);
@@ -928,12 +1006,16 @@ template <class T> int limit_impl(swe_hweno_ctx* c, const T* state, T* dmod) {
 
 template <class T> int alpha_impl(swe_hweno_ctx* c, const T* state, double* alpha_host) {
   if (!c || !state || !alpha_host || !is_type<T>(c)) return SWE_EINVAL;
-  launch_alpha<T>(c, state, c->sc->a_rhs, c->stream);
-  unsigned long long u[2];
-  if (hipMemcpyAsync(u, c->sc->a_rhs, sizeof u, hipMemcpyDeviceToHost, c->stream) != hipSuccess) return SWE_EHIP;
+  launch_alpha<T>(c, state, SP_RHS, c->stream);
+  unsigned long long u[ASET];
+  if (hipMemcpyAsync(u, speeds_set(c, SP_RHS), sizeof u, hipMemcpyDeviceToHost, c->stream) != hipSuccess)
+    return SWE_EHIP;
   const int e = take_device_error(c);
-  std::memcpy(&alpha_host[0], &u[0], 8);
-  std::memcpy(&alpha_host[1], &u[1], 8);
+  for (int k = 0; k < 2; ++k) {  // bits of non-negative doubles order as the doubles do
+    unsigned long long m = 0;
+    for (int l = 0; l < ASLOTS; ++l) m = std::max(m, u[l * ASTRIDE + k]);
+    std::memcpy(&alpha_host[k], &m, 8);
+  }
   return e;
 }
 
@@ -943,7 +1025,7 @@ template <class T> int step_impl(swe_hweno_ctx* c, T* state, double dt, double* 
   const swe_hweno_params saved = c->p;
   if (dt > 0) { c->p.flags |= SWE_FIXED_DT; c->p.fixed_dt = dt; }
   hipLaunchKernelGGL(k_clock, dim3(1), dim3(64), 0, c->stream, c->sc, 0.0);
-  launch_alpha<T>(c, state, c->sc->a_next, c->stream);
+  launch_alpha<T>(c, state, SP_NEXT, c->stream);
   enqueue_step<T>(c, state, 0, c->stream);
   c->p = saved;
   if (hipGetLastError() != hipSuccess) return SWE_EHIP;
@@ -969,7 +1051,7 @@ template <class T> int run_impl(swe_hweno_ctx* c, T* state, int nsteps, double t
   }
   // t = 0, t_end, steps = 0 and alpha of the initial state
   hipLaunchKernelGGL(k_clock, dim3(1), dim3(64), 0, c->stream, c->sc, t_end);
-  launch_alpha<T>(c, state, c->sc->a_next, c->stream);
+  launch_alpha<T>(c, state, SP_NEXT, c->stream);
   if (hipGetLastError() != hipSuccess) return SWE_EHIP;
   int done = 0;
   const int chunk = 64;
@@ -1007,19 +1089,21 @@ template <class T> int run_impl(swe_hweno_ctx* c, T* state, int nsteps, double t
   return e;
 }
 
-// Device address of `scratch` on the current device, looked up once per device.
+// Device addresses of `scratch` and `scratch_speeds` on the current device, looked up once per device.
 std::mutex g_scratch_mu;
-std::map<int, void*> g_scratch_addr;
+struct ScratchAddr { void* planes; void* speeds; };
+std::map<int, ScratchAddr> g_scratch_addr;
 
-int scratch_address(void** out) {
+int scratch_address(ScratchAddr* out) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return SWE_EHIP;
   std::lock_guard<std::mutex> lk(g_scratch_mu);
   auto it = g_scratch_addr.find(dev);
   if (it == g_scratch_addr.end()) {
-    void* ptr = nullptr;
-    if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr) return SWE_EHIP;
-    it = g_scratch_addr.emplace(dev, ptr).first;
+    ScratchAddr a{nullptr, nullptr};
+    if (hipGetSymbolAddress(&a.planes, HIP_SYMBOL(scratch)) != hipSuccess || !a.planes) return SWE_EHIP;
+    if (hipGetSymbolAddress(&a.speeds, HIP_SYMBOL(scratch_speeds)) != hipSuccess || !a.speeds) return SWE_EHIP;
+    it = g_scratch_addr.emplace(dev, a).first;
   }
   *out = it->second;
   return SWE_OK;
@@ -1038,8 +1122,8 @@ int step_noalloc_impl(const swe_hweno_params* p, double* state, const double* b,
   if (!params_ok(p) || !state || !b || !bx || (p->dim == 2 && !by)) return SWE_EINVAL;
   if (!(dt <= DBL_MAX)) return SWE_EINVAL;
   if (noalloc_bytes(p) > NOALLOC_BYTES) return SWE_EINVAL;
-  void* base = nullptr;
-  if (const int e = scratch_address(&base)) return e;
+  ScratchAddr at{nullptr, nullptr};
+  if (const int e = scratch_address(&at)) return e;
   // a context on the host stack that points into the scratch array and at the caller's bottom
   swe_hweno_ctx c;
   c.p = *p;
@@ -1050,8 +1134,9 @@ int step_noalloc_impl(const swe_hweno_params* p, double* state, const double* b,
   c.b = (void*)b;
   c.bx = (void*)bx;
   c.by = (void*)by;
-  c.sc = (DevScal*)base;
-  double* planes = (double*)((char*)base + NOALLOC_SCAL);
+  c.sc = (DevScal*)at.planes;
+  c.sp = (unsigned long long*)at.speeds;
+  double* planes = (double*)((char*)at.planes + NOALLOC_SCAL);
   c.S1 = planes;
   c.S2 = planes + (size_t)c.nf * c.n;
   c.Dn = planes + (size_t)2 * c.nf * c.n;
@@ -1063,10 +1148,10 @@ int step_noalloc_impl(const swe_hweno_params* p, double* state, const double* b,
     c.rows = choose_rows(p->nx, p->dim == 2 ? p->ny : 1, 4 * cus);
   }
   if (dt > 0) { c.p.flags |= SWE_FIXED_DT; c.p.fixed_dt = dt; }
-  hipLaunchKernelGGL(k_noalloc_setup, dim3(1), dim3(64), 0, c.stream, c.sc, dbits(p->alpha_x),
+  hipLaunchKernelGGL(k_noalloc_setup, dim3(1), dim3(ASLOTS), 0, c.stream, c.sc, c.sp, dbits(p->alpha_x),
                      dbits(p->dim == 2 ? p->alpha_y : 0.0));
   hipLaunchKernelGGL(k_clock, dim3(1), dim3(64), 0, c.stream, c.sc, 0.0);
-  launch_alpha<double>(&c, state, c.sc->a_next, c.stream);
+  launch_alpha<double>(&c, state, SP_NEXT, c.stream);
   enqueue_step<double>(&c, state, 0, c.stream);
   if (hipGetLastError() != hipSuccess) return SWE_EHIP;
   if (dt_used) {
@@ -1130,6 +1215,7 @@ void swe_hweno_destroy(swe_hweno_ctx* c) {
   if (c->S2) (void)hipFree(c->S2);
   if (c->Dn) (void)hipFree(c->Dn);
   if (c->sc) (void)hipFree(c->sc);
+  if (c->sp) (void)hipFree(c->sp);
   swe_adj_release(c);
   delete c;
 }
