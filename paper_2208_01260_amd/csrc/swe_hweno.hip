@@ -46,7 +46,8 @@ enum { ERR_DRY = 1, ERR_NONFINITE = 2 };
 // Device scalars of a context.
 struct DevScal {
   double dt, t, t_end, pad0;
-  int active, steps, err, pad1;
+  int active, steps, err;
+  int err0;  // batch: what the first stage of the running step met (see step_start)
 };
 
 // A set of Lax-Friedrichs speeds: (alpha_x, alpha_y) (bits of positive doubles) in each of
@@ -58,7 +59,9 @@ struct DevScal {
 constexpr int ASTRIDE = 16;  // 64-bit words per slot
 constexpr int ASLOTS = 64;   // slots of a context's sets
 constexpr int ASET = ASLOTS * ASTRIDE;
-enum { SP_N = 0, SP_1, SP_2, SP_NEXT, SP_FIX, SP_RHS, SP_SETS };  // alpha of U^n, U^(1), U^(2), U^(n+1), fixed, bare RHS
+// alpha of U^n, U^(1), U^(2), fixed, and of a bare right-hand side. A stage reads one of the first three,
+// fills the next and clears the one before: nothing else touches that one while it runs.
+enum { SP_N = 0, SP_1, SP_2, SP_FIX, SP_RHS, SP_SETS };
 
 template <class T>
 struct KArgs {
@@ -72,10 +75,14 @@ struct KArgs {
   T* Dn_out;              // stage 0: D^{n,mod}
   const unsigned long long* a_in;  // Lax-Friedrichs speeds used
   unsigned long long* a_out;       // max-reduction of the output state's speeds
+  unsigned long long* a_clear;     // the set this stage clears
+  const unsigned long long* a_n;   // first stage: speeds of U^n, for the CFL step
   DevScal* sc;
   int amask;                       // slots of the sets of speeds, less one
   int nx, ny, bcx, bcy, limiter, rows;
   T dx, dy, idx, idy, g, eps;
+  double cfl, fdt, cdx, cdy;       // first stage: the CFL step's parameters in double
+  int fixed_dt, use_tend;
 };
 
 // Largest finite value of the arithmetic type.
@@ -86,8 +93,8 @@ template <> __device__ __forceinline__ constexpr float big_value<float>() { retu
 __device__ __forceinline__ double bits2d(unsigned long long u) { return __longlong_as_double((long long)u); }
 
 // CFL time step from the Lax-Friedrichs speeds, rounded operation by operation (no contraction)
-// so that every kernel that computes it gets the same bits.
-__device__ __noinline__ double cfl_step(int dim, double cfl, double ax, double ay, double dx, double dy) {
+// so that every wavefront and kernel that computes it gets the same bits.
+__device__ __forceinline__ double cfl_step(int dim, double cfl, double ax, double ay, double dx, double dy) {
 #pragma clang fp contract(off)
   return dim == 2 ? cfl / (ax / dx + ay / dy) : cfl / (ax / dx);
 }
@@ -271,8 +278,60 @@ __device__ __forceinline__ void read_speeds(const unsigned long long* __restrict
   ay = uniform(wave_max(bits2d(q[1])));
 }
 
+// Time step of a stage's wavefront; false if the step does nothing. Every wavefront of the first stage forms it
+// for itself from the speeds of U^n (the CFL step or a fixed one, clipped at t_end), and the first tile's
+// leaves it for the other stages, instead of a one-thread kernel in front of the stages, which costs 4.5 us
+// on this device whatever it does. What the first stage decides by (t, t_end, the speeds of U^n and, in a batch, the
+// error flag) is written only by the other stages: the clock and the cleared set by the second stage, and a
+// batch's first stage flags errors in err0, which the second stage folds into err.
+template <class T, int DIM, int MODE, bool BATCH>
+__device__ __forceinline__ bool step_start(const KArgs<T>& a, bool first_tile, double sax, double say, double& dt) {
+  const int lane = (int)threadIdx.x;
+  DevScal* s = a.sc;
+  if (MODE == MODE_STAGE0) {
+    if (a.fixed_dt) {
+      dt = a.fdt;
+    } else {
+      if (a.a_n != a.a_in) read_speeds(a.a_n, a.amask, sax, say);
+      dt = uniform(cfl_step(DIM, a.cfl, sax, say, a.cdx, a.cdy));
+    }
+    bool active = true, bad = false;
+    if (a.use_tend) {
+      const double t = s->t, t_end = s->t_end;
+      if (!(t < t_end)) { active = false; dt = 0.0; }
+      else if (t + dt > t_end) dt = t_end - t;
+    }
+    if (BATCH && s->err) {  // the last step met a dry or non-finite node: this instance stops
+      active = false;
+      dt = 0.0;
+    } else if (!(dt > 0.0) || !(dt <= DBL_MAX)) {
+      bad = active;
+      active = false;
+    }
+    if (first_tile && lane == 0) {
+      s->dt = dt;
+      s->active = active ? 1 : 0;
+      if (bad) atomicOr(BATCH ? &s->err0 : &s->err, ERR_NONFINITE);
+    }
+    if (!active) return false;
+  } else {
+    if (BATCH && MODE == MODE_STAGE1 && first_tile && lane == 0 && s->err0) {
+      atomicOr(&s->err, s->err0);
+      s->err0 = 0;
+    }
+    if (s->active == 0) return false;
+    dt = s->dt;
+    if (MODE == MODE_STAGE1 && first_tile && lane == 0) { s->t += dt; s->steps += 1; }
+  }
+  if (first_tile && lane <= a.amask) {
+    unsigned long long* q = a.a_clear + (size_t)lane * ASTRIDE;
+    q[0] = q[1] = 0ull;
+  }
+  return true;
+}
+
 template <class T>
-__device__ __forceinline__ void flush_speeds(const KArgs<T>& a, int slot, T ax, T ay, int err) {
+__device__ __forceinline__ void flush_speeds(const KArgs<T>& a, int* errp, int slot, T ax, T ay, int err) {
   ax = wave_max(ax);
   ay = wave_max(ay);
   int e = err;
@@ -282,15 +341,14 @@ __device__ __forceinline__ void flush_speeds(const KArgs<T>& a, int slot, T ax, 
     unsigned long long* o = a.a_out + (size_t)(slot & a.amask) * ASTRIDE;
     atomicMax(&o[0], (unsigned long long)__double_as_longlong((double)ax));
     atomicMax(&o[1], (unsigned long long)__double_as_longlong((double)ay));
-    if (e) atomicOr(&a.sc->err, e);
+    if (e) atomicOr(errp, e);
   }
 }
 
 // --------------------------------------------------------------------------- the fused stage
 // One wavefront's tile: output columns [tx*60, tx*60+60) of rows [ty*rows, ty*rows+rows).
-template <class T, int DIM, int MODE>
+template <class T, int DIM, int MODE, bool BATCH>
 __device__ __forceinline__ void stage_tile(const KArgs<T>& a, int tx, int ty) {
-  if (MODE != MODE_RHS && a.sc->active == 0) return;
   __shared__ T sn[NNODE][WAVE];  // x-frame fluxes of the current row, one node per lane
   __shared__ T sf[14][WAVE];     // x-interface quantities (lane l: interface left of its column)
   __shared__ T sy[14][WAVE];     // y-interface quantities of the previous row (own lane)
@@ -301,24 +359,26 @@ __device__ __forceinline__ void stage_tile(const KArgs<T>& a, int tx, int ty) {
   const int r1 = DIM == 2 ? min(r0 + a.rows, a.ny) : 1;
   const bool col_out = lane >= 2 && lane < WAVE - 2 && c < a.nx;
   const int cq = col_out ? c : 0;  // a column that is always inside the grid
-  double sax, say;
-  read_speeds(a.a_in, a.amask, sax, say);
-  const T axl = T(sax), ayl = T(say);
   const size_t n = (size_t)a.nx * (DIM == 2 ? a.ny : 1);
-  const T dt = MODE == MODE_RHS ? T(0.0) : T(a.sc->dt);
   const int nu = DIM == 2 ? 3 : 2, nd = DIM == 2 ? 6 : 2;
   const int la = max(lane - 2, 0), lb = max(lane - 1, 0), ld = min(lane + 1, WAVE - 1);
   T amx = T(0.0), amy = T(0.0);
   int err = 0;
 
   // y window: raw records of rows r-1, r, r+1 (2D); the flux of interface r-1/2 waits in sy
-  T wm1[NREC], w0[NREC], wp1[NREC];
+  T wm2[NREC], wm1[NREC], w0[NREC], wp1[NREC];
+  load_rec<DIM>(a, a.S, c, r0, w0);
   if (DIM == 2) {
-    T wm2[NREC];
     load_rec<DIM>(a, a.S, c, r0 - 2, wm2);
     load_rec<DIM>(a, a.S, c, r0 - 1, wm1);
-    load_rec<DIM>(a, a.S, c, r0, w0);
     load_rec<DIM>(a, a.S, c, r0 + 1, wp1);
+  }
+  // the speeds and the step's scalars arrive while the window does
+  double sax, say, dtd = 0.0;
+  read_speeds(a.a_in, a.amask, sax, say);
+  if (MODE != MODE_RHS && !step_start<T, DIM, MODE, BATCH>(a, tx == 0 && ty == 0, sax, say, dtd)) return;
+  const T axl = T(sax), ayl = T(say), dt = T(dtd);
+  if (DIM == 2) {
     yring_store(syf, r0 - 2, lane, wm2, a.g);
     yring_store(syf, r0 - 1, lane, wm1, a.g);
     yring_store(syf, r0, lane, w0, a.g);
@@ -332,8 +392,6 @@ __device__ __forceinline__ void stage_tile(const KArgs<T>& a, int tx, int ty) {
     ifo_to_array(o, v);
 #pragma unroll
     for (int k = 0; k < 14; ++k) sy[k][lane] = v[k];
-  } else {
-    load_rec<DIM>(a, a.S, c, 0, w0);
   }
 
   for (int r = r0; r < r1; ++r) {
@@ -498,7 +556,7 @@ __device__ __forceinline__ void stage_tile(const KArgs<T>& a, int tx, int ty) {
     }
   }
   if (MODE != MODE_RHS) {
-    flush_speeds(a, tx + ty, amx, amy, err);
+    flush_speeds(a, BATCH && MODE == MODE_STAGE0 ? &a.sc->err0 : &a.sc->err, tx + ty, amx, amy, err);
   } else {
     int e = err;
 #pragma unroll
@@ -522,7 +580,7 @@ template <class T, int DIM, int MODE>
 __global__ __launch_bounds__(WAVE) void k_stage(KArgs<T> a) {
   const unsigned gx = gridDim.x;
   const unsigned t = band_tile(blockIdx.x + blockIdx.y * gx, gx * gridDim.y);
-  stage_tile<T, DIM, MODE>(a, (int)(t % gx), (int)(t / gx));
+  stage_tile<T, DIM, MODE, false>(a, (int)(t % gx), (int)(t / gx));
 }
 
 // --------------------------------------------------------------------------- small kernels
@@ -562,11 +620,6 @@ __global__ __launch_bounds__(256) void k_alpha(const T* __restrict__ S, const T*
   block_speeds(ax, ay, err, out, amask, errp);
 }
 
-// Set a pair of words.
-__global__ void k_set2(unsigned long long* p, unsigned long long v0, unsigned long long v1) {
-  if (threadIdx.x == 0) { p[0] = v0; p[1] = v1; }
-}
-
 // Set a set of ASLOTS speeds to given values (one wavefront).
 __global__ void k_set_speeds(unsigned long long* p, unsigned long long v0, unsigned long long v1) {
   unsigned long long* q = p + (size_t)threadIdx.x * ASTRIDE;
@@ -574,9 +627,50 @@ __global__ void k_set_speeds(unsigned long long* p, unsigned long long v0, unsig
   q[1] = threadIdx.x == 0 ? v1 : 0ull;
 }
 
-// Reset the clock of a run or a single step (the error flag is left alone).
-__global__ void k_clock(DevScal* s, double t_end) {
-  if (threadIdx.x == 0) { s->t = 0.0; s->t_end = t_end; s->dt = 0.0; s->active = 1; s->steps = 0; }
+// Reset the clock of a run or a single step (the error flag is left alone) and clear the sets of speeds
+// of its stages. One wavefront.
+__device__ __forceinline__ void reset_run(DevScal* s, unsigned long long* sp, double t_end, int l) {
+  if (l == 0) { s->t = 0.0; s->t_end = t_end; s->dt = 0.0; s->active = 1; s->steps = 0; }
+  unsigned long long* q = sp + (size_t)l * ASTRIDE;
+  q[SP_1 * ASET] = q[SP_1 * ASET + 1] = q[SP_2 * ASET] = q[SP_2 * ASET + 1] = 0ull;
+}
+__global__ void k_reset(DevScal* s, unsigned long long* sp, double t_end) {
+  reset_run(s, sp, t_end, (int)threadIdx.x);
+  unsigned long long* q = sp + SP_N * ASET + (size_t)threadIdx.x * ASTRIDE;
+  q[0] = q[1] = 0ull;
+}
+
+// The same and the speeds of the state in one launch, for a grid small enough that at most one workgroup
+// of 1024 per slot reads it quickly: each writes its slot, so nothing need be cleared first. With begin set, it also
+// resets the clock. A launch saved is 4.5 us.
+constexpr int START_THREADS = 1024;
+template <class T, int DIM>
+__global__ __launch_bounds__(START_THREADS) void k_start(const T* __restrict__ S, const T* __restrict__ b, size_t n, T g,
+                                                         unsigned long long* sp, int set, DevScal* s, int begin,
+                                                         double t_end) {
+  __shared__ double sx[START_THREADS / WAVE], sy[START_THREADS / WAVE];
+  T ax = T(0.0), ay = T(0.0);
+  int err = 0;
+  for (size_t q = (size_t)blockIdx.x * START_THREADS + threadIdx.x; q < n; q += (size_t)gridDim.x * START_THREADS)
+    speeds(S[q], S[n + q], DIM == 2 ? S[2 * n + q] : T(0.0), b[q], g, ax, ay, err);
+  ax = wave_max(ax);
+  ay = wave_max(ay);
+  if (err) atomicOr(&s->err, err);
+  const int w = (int)(threadIdx.x / WAVE), l = (int)(threadIdx.x % WAVE);
+  if (l == 0) { sx[w] = (double)ax; sy[w] = (double)ay; }
+  __syncthreads();
+  if (w != 0) return;
+  const double mx = wave_max(l < START_THREADS / WAVE ? sx[l] : 0.0), my = wave_max(l < START_THREADS / WAVE ? sy[l] : 0.0);
+  unsigned long long* out = sp + (size_t)set * ASET;
+  if (l == 0) {
+    unsigned long long* o = out + (size_t)blockIdx.x * ASTRIDE;
+    o[0] = (unsigned long long)__double_as_longlong(mx);
+    o[1] = (unsigned long long)__double_as_longlong(my);
+  }
+  if (blockIdx.x == 0) {
+    if (l >= (int)gridDim.x) out[(size_t)l * ASTRIDE] = out[(size_t)l * ASTRIDE + 1] = 0ull;
+    if (begin) reset_run(s, sp, t_end, l);
+  }
 }
 
 __global__ void k_clear_err(DevScal* s) {
@@ -601,48 +695,20 @@ static_assert(sizeof(DevScal) <= NOALLOC_SCAL, "device scalars must fit their sl
 static __device__ __align__(256) unsigned char scratch[NOALLOC_BYTES];
 static __device__ __align__(256) unsigned long long scratch_speeds[SP_SETS * ASET];
 
-// Start of an allocation-free step: the fixed speeds and a cleared error flag (the array keeps
-// whatever the previous call on this GPU left). One wavefront.
-__global__ void k_noalloc_setup(DevScal* s, unsigned long long* sp, unsigned long long afx, unsigned long long afy) {
-  unsigned long long* q = sp + SP_FIX * ASET + (size_t)threadIdx.x * ASTRIDE;
-  q[0] = threadIdx.x == 0 ? afx : 0ull;
-  q[1] = threadIdx.x == 0 ? afy : 0ull;
-  if (threadIdx.x == 0) s->err = 0;
-}
-
-// Start of a step: alpha of U^n from the previous step's reduction, the CFL step (or fixed),
-// clipped at t_end; clears the reductions this step fills. One wavefront, a lane per slot in use.
-__global__ void k_prologue(DevScal* s, unsigned long long* sp, int amask, int dim, int fixed_dt, double fdt, double cfl, double dx,
-                           double dy, int use_tend) {
+// The device scalars of a new context (or of an allocation-free step, whose array keeps whatever the
+// previous call on this GPU left): the fixed speeds, everything else zero. One wavefront.
+__global__ void k_setup(DevScal* s, unsigned long long* sp, unsigned long long afx, unsigned long long afy) {
   const int l = (int)threadIdx.x;
-  if (l > amask) return;
-  unsigned long long* nx = sp + SP_NEXT * ASET + l * ASTRIDE;
-  const unsigned long long u0 = nx[0], u1 = nx[1];
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    unsigned long long* q = sp + (k == 0 ? SP_N : (k == 1 ? SP_1 : (k == 2 ? SP_2 : SP_NEXT))) * ASET + l * ASTRIDE;
-    q[0] = k == 0 ? u0 : 0ull;
-    q[1] = k == 0 ? u1 : 0ull;
+  for (int k = 0; k < SP_SETS; ++k) {
+    unsigned long long* q = sp + (size_t)k * ASET + (size_t)l * ASTRIDE;
+    q[0] = k == SP_FIX && l == 0 ? afx : 0ull;
+    q[1] = k == SP_FIX && l == 0 ? afy : 0ull;
   }
-  double ax = bits2d(u0), ay = bits2d(u1);
-  if (amask != 0) {
-    ax = wave_max(ax);
-    ay = wave_max(ay);
+  if (l == 0) {
+    s->dt = s->t = s->t_end = s->pad0 = 0.0;
+    s->active = s->steps = s->err = s->err0 = 0;
   }
-  if (l != 0) return;
-  double dt = fixed_dt ? fdt : cfl_step(dim, cfl, ax, ay, dx, dy);
-  int active = 1;
-  if (use_tend) {
-    if (!(s->t < s->t_end)) { active = 0; dt = 0.0; }
-    else if (s->t + dt > s->t_end) dt = s->t_end - s->t;
-  }
-  if (!(dt > 0.0) || !(dt <= DBL_MAX)) {
-    if (active) s->err |= ERR_NONFINITE;
-    active = 0;
-  }
-  s->active = active;
-  s->dt = dt;
-  if (active) { s->t += dt; s->steps += 1; }
 }
 
 // Stand-alone limiter: one thread per node, neighbours read directly.
@@ -686,6 +752,7 @@ struct swe_hweno_ctx {
   hipStream_t cap = nullptr;  // capture stream for the per-step graphs
   int nf = 0, nd = 0;
   size_t n = 0;
+  void* mem = nullptr;        // the one device allocation that the pointers below point into
   void *b = nullptr, *bx = nullptr, *by = nullptr;  // planes of the context's type
   void *S1 = nullptr, *S2 = nullptr, *Dn = nullptr;
   DevScal* sc = nullptr;
@@ -749,6 +816,8 @@ dim3 stage_grid(const swe_hweno_ctx* c) {
   return dim3(gx, gy, 1);
 }
 
+unsigned long long* speeds_set(const swe_hweno_ctx* c, int set) { return c->sp + (size_t)set * ASET; }
+
 // Slots in use, less one: one slot up to 48 wavefronts in a stage (their atomics queue for under 1 us, about
 // what reading and reducing 64 slots costs each of a step's kernels), else all.
 int speeds_mask(const swe_hweno_ctx* c) {
@@ -771,7 +840,18 @@ template <class T> KArgs<T> base_args(const swe_hweno_ctx* c) {
   a.idx = T(1.0 / dx); a.idy = T(1.0 / dy);
   a.g = T(c->p.g); a.eps = T(c->p.eps);
   a.rows = c->rows;
+  a.cfl = c->p.cfl; a.fdt = c->p.fixed_dt; a.cdx = dx; a.cdy = dy;
+  a.fixed_dt = (c->p.flags & SWE_FIXED_DT) ? 1 : 0;
   return a;
+}
+
+// Speeds read, filled and cleared by the stages of a step (the first stage also forms the step from those of U^n).
+template <class T> void stage_speeds(const swe_hweno_ctx* c, KArgs<T>& a, int stage) {
+  const bool fa = (c->p.flags & SWE_FIXED_ALPHA) != 0;
+  a.a_in = speeds_set(c, fa ? SP_FIX : stage);
+  a.a_out = speeds_set(c, (stage + 1) % 3);
+  a.a_clear = speeds_set(c, (stage + 2) % 3);
+  a.a_n = speeds_set(c, SP_N);
 }
 
 template <class T, int MODE> void launch_stage_mode(const swe_hweno_ctx* c, const KArgs<T>& a, hipStream_t s) {
@@ -779,20 +859,33 @@ template <class T, int MODE> void launch_stage_mode(const swe_hweno_ctx* c, cons
   else hipLaunchKernelGGL((k_stage<T, 1, MODE>), stage_grid(c), dim3(WAVE), 0, s, a);
 }
 
-unsigned long long* speeds_set(const swe_hweno_ctx* c, int set) { return c->sp + (size_t)set * ASET; }
-
-template <class T> void launch_alpha(const swe_hweno_ctx* c, const T* S, int set, hipStream_t s) {
+// Speeds of a state into a set; with begin (set SP_N), at the start of a run or step whose clock it resets.
+template <class T> void launch_alpha(const swe_hweno_ctx* c, const T* S, int set, bool begin, double t_end, hipStream_t s) {
+  const T* b = (const T*)c->b;
+  const int amask = speeds_mask(c);
+  // one launch while a workgroup has at most four nodes per thread (in one slot at most 16): at 400^2 4.9 us
+  // against 4.5 + 5.4 us of the two launches
+  const size_t most = amask ? (size_t)4 * ASLOTS * START_THREADS : (size_t)16 * START_THREADS;
+  if (c->n <= most) {
+    const size_t blocks = amask ? std::min<size_t>((c->n + START_THREADS - 1) / START_THREADS, ASLOTS) : 1;
+    if (c->p.dim == 2)
+      hipLaunchKernelGGL((k_start<T, 2>), dim3((unsigned)blocks), dim3(START_THREADS), 0, s, S, b, c->n, T(c->p.g), c->sp,
+                         set, c->sc, begin ? 1 : 0, t_end);
+    else
+      hipLaunchKernelGGL((k_start<T, 1>), dim3((unsigned)blocks), dim3(START_THREADS), 0, s, S, b, c->n, T(c->p.g), c->sp,
+                         set, c->sc, begin ? 1 : 0, t_end);
+    return;
+  }
   unsigned long long* out = speeds_set(c, set);
-  hipLaunchKernelGGL(k_set_speeds, dim3(1), dim3(ASLOTS), 0, s, out, 0ull, 0ull);
+  if (begin) hipLaunchKernelGGL(k_reset, dim3(1), dim3(ASLOTS), 0, s, c->sc, c->sp, t_end);
+  else hipLaunchKernelGGL(k_set_speeds, dim3(1), dim3(ASLOTS), 0, s, out, 0ull, 0ull);
   // a node per thread up to eight workgroups per CU, which fill the memory system; each ends in one pair of atomics
   const size_t blocks = (c->n + 255) / 256;
   const unsigned grid = (unsigned)(blocks < 2048 ? blocks : 2048);
   if (c->p.dim == 2)
-    hipLaunchKernelGGL((k_alpha<T, 2>), dim3(grid), dim3(256), 0, s, S, (const T*)c->b, c->n, T(c->p.g), out, speeds_mask(c),
-                       &c->sc->err);
+    hipLaunchKernelGGL((k_alpha<T, 2>), dim3(grid), dim3(256), 0, s, S, b, c->n, T(c->p.g), out, amask, &c->sc->err);
   else
-    hipLaunchKernelGGL((k_alpha<T, 1>), dim3(grid), dim3(256), 0, s, S, (const T*)c->b, c->n, T(c->p.g), out, speeds_mask(c),
-                       &c->sc->err);
+    hipLaunchKernelGGL((k_alpha<T, 1>), dim3(grid), dim3(256), 0, s, S, b, c->n, T(c->p.g), out, amask, &c->sc->err);
 }
 
 hipEvent_t take_event(swe_hweno_ctx* c) {
@@ -835,33 +928,29 @@ void collect_timing(swe_hweno_ctx* c) {
   c->pending.clear();
 }
 
-// One step on stream s: prologue and three fused stages; U^n is `state`, updated in place.
+// One step on stream s: three fused stages; U^n is `state`, updated in place.
 // With timing on (direct launches only) every stage kernel is bracketed by an event pair.
 template <class T> void enqueue_step(swe_hweno_ctx* c, T* state, int use_tend, hipStream_t s) {
-  const KArgs<T> base = base_args<T>(c);
-  const bool fa = (c->p.flags & SWE_FIXED_ALPHA) != 0;
-  const double dx = (c->p.x1 - c->p.x0) / c->p.nx;
-  const double dy = c->p.dim == 2 ? (c->p.y1 - c->p.y0) / c->p.ny : 1.0;
-  hipLaunchKernelGGL(k_prologue, dim3(1), dim3(ASLOTS), 0, s, c->sc, c->sp, speeds_mask(c), c->p.dim, (c->p.flags & SWE_FIXED_DT) ? 1 : 0,
-                     c->p.fixed_dt, c->p.cfl, dx, dy, use_tend);
+  KArgs<T> base = base_args<T>(c);
+  base.use_tend = use_tend;
   T* S1 = (T*)c->S1;
   T* S2 = (T*)c->S2;
   T* Dn = (T*)c->Dn;
   KArgs<T> a = base;
+  stage_speeds(c, a, 0);
   a.S = state; a.out = S1; a.Dn_out = Dn;
-  a.a_in = speeds_set(c, fa ? SP_FIX : SP_N); a.a_out = speeds_set(c, SP_1);
   int id = time_begin(c, s);
   launch_stage_mode<T, MODE_STAGE0>(c, a, s);
   time_end(c, id, 1, s);
   a = base;
+  stage_speeds(c, a, 1);
   a.S = S1; a.Sn = state; a.Dn = Dn; a.out = S2;
-  a.a_in = speeds_set(c, fa ? SP_FIX : SP_1); a.a_out = speeds_set(c, SP_2);
   id = time_begin(c, s);
   launch_stage_mode<T, MODE_STAGE1>(c, a, s);
   time_end(c, id, 2, s);
   a = base;
+  stage_speeds(c, a, 2);
   a.S = S2; a.Sn = state; a.Dn = Dn; a.out = state;
-  a.a_in = speeds_set(c, fa ? SP_FIX : SP_2); a.a_out = speeds_set(c, SP_NEXT);
   id = time_begin(c, s);
   launch_stage_mode<T, MODE_STAGE2>(c, a, s);
   time_end(c, id, 3, s);
@@ -939,13 +1028,18 @@ int init_impl(const swe_hweno_params* p, const T* b, const T* bx, const T* by, v
   c->nd = p->dim == 2 ? 6 : 2;
   c->n = (size_t)p->nx * (size_t)(p->dim == 2 ? p->ny : 1);
   const size_t plane = c->n * sizeof(T);
-  bool ok = hipMalloc(&c->b, plane * 3) == hipSuccess;
-  ok = ok && hipMalloc(&c->S1, plane * c->nf) == hipSuccess;
-  ok = ok && hipMalloc(&c->S2, plane * c->nf) == hipSuccess;
-  ok = ok && hipMalloc(&c->Dn, plane * c->nd) == hipSuccess;
-  ok = ok && hipMalloc(&c->sc, sizeof(DevScal)) == hipSuccess;
-  ok = ok && hipMalloc(&c->sp, sizeof(unsigned long long) * SP_SETS * ASET) == hipSuccess;
-  if (!ok) { swe_hweno_destroy(c); return SWE_ENOMEM; }
+  // one allocation: the scalars, the sets of speeds and the planes, each on a boundary of 256 bytes
+  const auto up = [](size_t v) { return (v + 255) / 256 * 256; };
+  const size_t at_sp = up(sizeof(DevScal)), at_b = up(at_sp + sizeof(unsigned long long) * SP_SETS * ASET);
+  const size_t at_s1 = up(at_b + 3 * plane), at_s2 = up(at_s1 + c->nf * plane), at_dn = up(at_s2 + c->nf * plane);
+  if (hipMalloc(&c->mem, at_dn + c->nd * plane) != hipSuccess) { swe_hweno_destroy(c); return SWE_ENOMEM; }
+  char* base = (char*)c->mem;
+  c->sc = (DevScal*)base;
+  c->sp = (unsigned long long*)(base + at_sp);
+  c->b = base + at_b;
+  c->S1 = base + at_s1;
+  c->S2 = base + at_s2;
+  c->Dn = base + at_dn;
   c->bx = (T*)c->b + c->n;
   c->by = (T*)c->b + 2 * c->n;
   {
@@ -955,17 +1049,14 @@ int init_impl(const swe_hweno_params* p, const T* b, const T* bx, const T* by, v
       cus = 256;
     c->rows = choose_rows(p->nx, p->dim == 2 ? p->ny : 1, 4 * cus);
   }
-  ok = hipStreamCreateWithFlags(&c->cap, hipStreamNonBlocking) == hipSuccess;
+  bool ok = hipStreamCreateWithFlags(&c->cap, hipStreamNonBlocking) == hipSuccess;
   ok = ok && hipMemcpyAsync(c->b, b, plane, hipMemcpyDeviceToDevice, c->stream) == hipSuccess;
   ok = ok && hipMemcpyAsync(c->bx, bx, plane, hipMemcpyDeviceToDevice, c->stream) == hipSuccess;
   if (p->dim == 2) ok = ok && hipMemcpyAsync(c->by, by, plane, hipMemcpyDeviceToDevice, c->stream) == hipSuccess;
   else ok = ok && hipMemsetAsync(c->by, 0, plane, c->stream) == hipSuccess;
-  DevScal init;
-  std::memset(&init, 0, sizeof init);
-  hipLaunchKernelGGL(k_set_speeds, dim3(1), dim3(ASLOTS), 0, c->stream, speeds_set(c, SP_FIX), dbits(p->alpha_x),
+  hipLaunchKernelGGL(k_setup, dim3(1), dim3(ASLOTS), 0, c->stream, c->sc, c->sp, dbits(p->alpha_x),
                      dbits(p->dim == 2 ? p->alpha_y : 0.0));
   ok = ok && hipGetLastError() == hipSuccess;
-  ok = ok && hipMemcpyAsync(c->sc, &init, sizeof init, hipMemcpyHostToDevice, c->stream) == hipSuccess;
   ok = ok && hipStreamSynchronize(c->stream) == hipSuccess;
   if (!ok) { swe_hweno_destroy(c); return SWE_EHIP; }
   *out = c;
@@ -980,7 +1071,7 @@ template <class T> int rhs_impl(swe_hweno_ctx* c, const T* state, T* rhs, double
   if (alpha_x > 0 && c->p.dim == 2 && !(alpha_y > 0 && std::isfinite(alpha_y))) return SWE_EINVAL;
   const size_t bytes = c->n * c->nf * sizeof(T);
   if ((const char*)rhs < (const char*)state + bytes && (const char*)state < (const char*)rhs + bytes) return SWE_EINVAL;
-  if (alpha_x < 0) launch_alpha<T>(c, state, SP_RHS, c->stream);
+  if (alpha_x < 0) launch_alpha<T>(c, state, SP_RHS, false, 0.0, c->stream);
   else
     hipLaunchKernelGGL(k_set_speeds, dim3(1), dim3(ASLOTS), 0, c->stream, speeds_set(c, SP_RHS), dbits(alpha_x),
                        dbits(c->p.dim == 2 ? alpha_y : 0.0));
@@ -1006,7 +1097,7 @@ template <class T> int limit_impl(swe_hweno_ctx* c, const T* state, T* dmod) {
 
 template <class T> int alpha_impl(swe_hweno_ctx* c, const T* state, double* alpha_host) {
   if (!c || !state || !alpha_host || !is_type<T>(c)) return SWE_EINVAL;
-  launch_alpha<T>(c, state, SP_RHS, c->stream);
+  launch_alpha<T>(c, state, SP_RHS, false, 0.0, c->stream);
   unsigned long long u[ASET];
   if (hipMemcpyAsync(u, speeds_set(c, SP_RHS), sizeof u, hipMemcpyDeviceToHost, c->stream) != hipSuccess)
     return SWE_EHIP;
@@ -1024,8 +1115,7 @@ template <class T> int step_impl(swe_hweno_ctx* c, T* state, double dt, double* 
   if (!(dt <= DBL_MAX)) return SWE_EINVAL;
   const swe_hweno_params saved = c->p;
   if (dt > 0) { c->p.flags |= SWE_FIXED_DT; c->p.fixed_dt = dt; }
-  hipLaunchKernelGGL(k_clock, dim3(1), dim3(64), 0, c->stream, c->sc, 0.0);
-  launch_alpha<T>(c, state, SP_NEXT, c->stream);
+  launch_alpha<T>(c, state, SP_N, true, 0.0, c->stream);
   enqueue_step<T>(c, state, 0, c->stream);
   c->p = saved;
   if (hipGetLastError() != hipSuccess) return SWE_EHIP;
@@ -1050,8 +1140,7 @@ template <class T> int run_impl(swe_hweno_ctx* c, T* state, int nsteps, double t
     c->g_tend = use_tend;
   }
   // t = 0, t_end, steps = 0 and alpha of the initial state
-  hipLaunchKernelGGL(k_clock, dim3(1), dim3(64), 0, c->stream, c->sc, t_end);
-  launch_alpha<T>(c, state, SP_NEXT, c->stream);
+  launch_alpha<T>(c, state, SP_N, true, t_end, c->stream);
   if (hipGetLastError() != hipSuccess) return SWE_EHIP;
   int done = 0;
   const int chunk = 64;
@@ -1148,10 +1237,9 @@ int step_noalloc_impl(const swe_hweno_params* p, double* state, const double* b,
     c.rows = choose_rows(p->nx, p->dim == 2 ? p->ny : 1, 4 * cus);
   }
   if (dt > 0) { c.p.flags |= SWE_FIXED_DT; c.p.fixed_dt = dt; }
-  hipLaunchKernelGGL(k_noalloc_setup, dim3(1), dim3(ASLOTS), 0, c.stream, c.sc, c.sp, dbits(p->alpha_x),
+  hipLaunchKernelGGL(k_setup, dim3(1), dim3(ASLOTS), 0, c.stream, c.sc, c.sp, dbits(p->alpha_x),
                      dbits(p->dim == 2 ? p->alpha_y : 0.0));
-  hipLaunchKernelGGL(k_clock, dim3(1), dim3(64), 0, c.stream, c.sc, 0.0);
-  launch_alpha<double>(&c, state, SP_NEXT, c.stream);
+  launch_alpha<double>(&c, state, SP_N, true, 0.0, c.stream);
   enqueue_step<double>(&c, state, 0, c.stream);
   if (hipGetLastError() != hipSuccess) return SWE_EHIP;
   if (dt_used) {
@@ -1205,17 +1293,12 @@ int swe_hweno_init_f32(const swe_hweno_params* p, const float* b, const float* b
 
 void swe_hweno_destroy(swe_hweno_ctx* c) {
   if (!c) return;
-  if (c->stream || c->b) (void)hipStreamSynchronize(c->stream);
+  if (c->stream || c->mem) (void)hipStreamSynchronize(c->stream);
   destroy_graphs(c);
   collect_timing(c);
   for (hipEvent_t e : c->pool) (void)hipEventDestroy(e);
   if (c->cap) (void)hipStreamDestroy(c->cap);
-  if (c->b) (void)hipFree(c->b);
-  if (c->S1) (void)hipFree(c->S1);
-  if (c->S2) (void)hipFree(c->S2);
-  if (c->Dn) (void)hipFree(c->Dn);
-  if (c->sc) (void)hipFree(c->sc);
-  if (c->sp) (void)hipFree(c->sp);
+  if (c->mem) (void)hipFree(c->mem);
   swe_adj_release(c);
   delete c;
 }
