@@ -179,7 +179,9 @@ int swe_hweno_run_f32(swe_hweno_ctx* ctx, float* state, int nsteps, double t_end
 int swe_hweno_tile(int* cols_per_wave, int* rows_per_wave);
 
 /* The tile a context uses: rows per march are chosen at init from the grid and the device's
- * compute-unit count (environment variable SWE_HWENO_ROWS overrides). Host-only. */
+ * compute-unit count (environment variable SWE_HWENO_ROWS overrides). A grid too small to fill the
+ * device takes rows per workgroup instead, whose wavefronts share the tile's work. The tile
+ * changes no bit of any result. Host-only. */
 int swe_hweno_ctx_tile(const swe_hweno_ctx* ctx, int* cols_per_wave, int* rows_per_wave);
 
 /* The library's own arithmetic building blocks, applied elementwise on the device for

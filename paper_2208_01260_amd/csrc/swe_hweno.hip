@@ -286,7 +286,7 @@ __device__ __forceinline__ void read_speeds(const unsigned long long* __restrict
 // batch's first stage flags errors in err0, which the second stage folds into err.
 template <class T, int DIM, int MODE, bool BATCH>
 __device__ __forceinline__ bool step_start(const KArgs<T>& a, bool first_tile, double sax, double say, double& dt) {
-  const int lane = (int)threadIdx.x;
+  const int lane = (int)(threadIdx.x & (WAVE - 1));
   DevScal* s = a.sc;
   if (MODE == MODE_STAGE0) {
     if (a.fixed_dt) {
@@ -337,7 +337,7 @@ __device__ __forceinline__ void flush_speeds(const KArgs<T>& a, int* errp, int s
   int e = err;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) e |= __shfl_xor(e, o, WAVE);
-  if (threadIdx.x == 0) {
+  if ((threadIdx.x & (WAVE - 1)) == 0) {
     unsigned long long* o = a.a_out + (size_t)(slot & a.amask) * ASTRIDE;
     atomicMax(&o[0], (unsigned long long)__double_as_longlong((double)ax));
     atomicMax(&o[1], (unsigned long long)__double_as_longlong((double)ay));
@@ -583,6 +583,187 @@ __global__ __launch_bounds__(WAVE) void k_stage(KArgs<T> a) {
   stage_tile<T, DIM, MODE, false>(a, (int)(t % gx), (int)(t / gx));
 }
 
+// --------------------------------------------------------------------------- the fused stage, small grids
+// The same stage for grids that cannot fill the GPU with marching wavefronts, where a stage takes as long as one
+// wavefront's serial work. A workgroup of W wavefronts takes 60 columns by R rows, shared out as tasks of one
+// wavefront each: the R + 1 y-interfaces of a row of columns (from four rows that the wavefront loads), the R rows' x-interfaces
+// and the R rows' limiters; the quantities meet in LDS and the rows are assembled and updated by thirds
+// (U, U_x, U_y). Bound by latency: launch, one trip for the rows, then the tasks, two wavefronts per SIMD at 8
+// wavefronts. A stage in FP64, against marching wavefronts: 61 x 47 7.7 us (R = 1, W = 4) against 19.3, 200 x 100 9.0
+// (R = 2) against 19.3, 256^2 15.3 (R = 6) against 20.3, 300^2 15.9 (R = 6) against 21.0.
+template <class T>
+struct SmallLds {
+  T (*x)[NNODE][WAVE];  // [R] x-frame fluxes of a row while its wavefront works, then the x-interface left of each column
+  T (*y)[14][WAVE];     // [R + 1] y-interface below row r
+  T (*d)[6][WAVE];      // [R] the limiter's neighbour values, then the limited derivatives
+};
+constexpr size_t small_lds_words(int R) { return (size_t)WAVE * (R * NNODE + (R + 1) * 14 + R * 6); }
+
+// Planes 3 THIRD .. 3 THIRD + 2 of one row: assembly, Runge-Kutta combination and stores. u, un, dn: the node's own state
+// (eta, H1, H2, m, w, b) and the values of U^n or D^{n,mod} for these planes, loaded before the interfaces were ready.
+template <class T, int MODE, int THIRD>
+__device__ __forceinline__ void small_update(const KArgs<T>& a, const SmallLds<T>& L, int row, size_t q, bool out, T dt,
+                                             const T u[6], const T base[3], int slot) {
+  const int lane = (int)(threadIdx.x & (WAVE - 1)), ld = min(lane + 1, WAVE - 1);
+  const size_t n = (size_t)a.nx * a.ny;
+  T xl[14], xr[14], yl[14], yr[14], Rv[9];
+#pragma unroll
+  for (int k = 0; k < 14; ++k) {
+    xl[k] = L.x[row][k][lane]; xr[k] = L.x[row][k][ld];
+    yl[k] = L.y[row][k][lane]; yr[k] = L.y[row + 1][k][lane];
+  }
+#pragma unroll
+  for (int k = 0; k < 9; ++k) Rv[k] = T(0.0);
+  assemble<0>(xl, xr, u[0], u[1], u[2], a.g, a.idx, Rv);
+  assemble<1>(yl, yr, u[0], u[1], u[2], a.g, a.idy, Rv);
+  T amx = T(0.0), amy = T(0.0);
+  int err = 0;
+  if (MODE == MODE_RHS) {
+    if (out) {
+      T z = T(0.0);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        a.out[(3 * THIRD + k) * n + q] = Rv[3 * THIRD + k];
+        z = fma(Rv[3 * THIRD + k], T(0.0), z);
+      }
+      if (THIRD == 0) {
+        const T h = u[0] - u[5];
+        if (!(h > T(0.0))) err |= (h == h) ? ERR_DRY : ERR_NONFINITE;
+      }
+      if (z != z) err |= ERR_NONFINITE;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) err |= __shfl_xor(err, o, WAVE);
+    if (lane == 0 && err) atomicOr(&a.sc->err, err);
+    return;
+  }
+  T v[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const T s0 = THIRD == 0 ? (k == 0 ? u[0] : (k == 1 ? u[3] : u[4])) : L.d[row][3 * (THIRD - 1) + k][lane];
+    const T s = s0 + dt * Rv[3 * THIRD + k];
+    if (MODE == MODE_STAGE0) v[k] = s;
+    else if (MODE == MODE_STAGE1) v[k] = (T(3.0) * base[k] + s) * T(0.25);
+    else v[k] = div3(base[k] + T(2.0) * s);
+    if (out) {
+      a.out[(3 * THIRD + k) * n + q] = v[k];
+      if (MODE == MODE_STAGE0 && THIRD > 0) a.Dn_out[(3 * (THIRD - 1) + k) * n + q] = s0;
+    }
+  }
+  if (THIRD == 0) {
+    if (out) speeds(v[0], v[1], v[2], u[5], a.g, amx, amy, err);
+    flush_speeds(a, &a.sc->err, slot, amx, amy, err);
+  }
+}
+
+template <class T, int MODE, int W>
+__global__ __launch_bounds__(W * WAVE) void k_small(KArgs<T> a) {
+  extern __shared__ __align__(16) unsigned char small_lds[];
+  const int R = a.rows;
+  SmallLds<T> L;
+  L.x = (T (*)[NNODE][WAVE])small_lds;
+  L.y = (T (*)[14][WAVE])(L.x + R);
+  L.d = (T (*)[6][WAVE])(L.y + R + 1);
+  const unsigned gx = gridDim.x;
+  const unsigned tile = band_tile(blockIdx.x + blockIdx.y * gx, gx * gridDim.y);
+  const int tx = (int)(tile % gx), ty = (int)(tile / gx);
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+  const int lane = (int)(threadIdx.x & (WAVE - 1));
+  const int c = tx * OUT_COLS - 2 + lane;
+  const int r0 = ty * R, nr = min(R, a.ny - r0);
+  const bool col_out = lane >= 2 && lane < WAVE - 2 && c < a.nx;
+  const int cq = col_out ? c : 0;
+  const size_t n = (size_t)a.nx * a.ny;
+  const int la = max(lane - 2, 0), lb = max(lane - 1, 0), ld = min(lane + 1, WAVE - 1);
+  double sax, say, dtd = 0.0;
+  read_speeds(a.a_in, a.amask, sax, say);
+  if (MODE != MODE_RHS && !step_start<T, 2, MODE, false>(a, tx == 0 && ty == 0 && w == 0, sax, say, dtd)) return;
+  const T axl = T(sax), ayl = T(say), dt = T(dtd);
+  const int ntask = 2 * nr + 1 + (MODE == MODE_RHS ? 0 : nr);
+  for (int task = w; task < ntask; task += W) {
+    if (task <= nr) {  // y-interface below row r0 + task
+      T r4[4][NREC];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) load_rec<2>(a, a.S, c, r0 + task - 2 + k, r4[k]);
+      IfO<T> o;
+      auto fy = [&](int k, NodeF<T>& X) { node_frame<1>(r4[k], a.g, X); };
+      interface_flux(fy, ayl, a.dy, a.eps, a.g, o);
+      T v[14];
+      ifo_to_array(o, v);
+#pragma unroll
+      for (int k = 0; k < 14; ++k) L.y[task][k][lane] = v[k];
+    } else if (task <= 2 * nr) {  // x-interfaces of a row
+      const int row = task - nr - 1;
+      T r1[NREC];
+      load_rec<2>(a, a.S, c, r0 + row, r1);
+      NodeF<T> me;
+      node_frame<0>(r1, a.g, me);
+      nodef_store(L.x[row], lane, me);
+      __builtin_amdgcn_wave_barrier();
+      IfO<T> o;
+      auto fx = [&](int k, NodeF<T>& X) {
+        if (k == 2) X = me;
+        else nodef_load(L.x[row], k == 0 ? la : (k == 1 ? lb : ld), X);
+      };
+      interface_flux(fx, axl, a.dx, a.eps, a.g, o);
+      T v[14];
+      ifo_to_array(o, v);
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int k = 0; k < 14; ++k) L.x[row][k][lane] = v[k];
+    } else {  // limited derivatives of a row
+      const int row = task - 2 * nr - 1;
+      T me[NREC];
+      load_rec<2>(a, a.S, c, r0 + row, me);
+      T Dm[6];
+      if (a.limiter) {
+        T ym[NREC], yp[NREC];
+        load_rec<2>(a, a.S, c, r0 + row - 1, ym);
+        load_rec<2>(a, a.S, c, r0 + row + 1, yp);
+        T (*sn)[WAVE] = L.d[row];
+#pragma unroll
+        for (int k = 0; k < 6; ++k) sn[k][lane] = me[k];  // eta, m, w, H1, M1, W1
+        __builtin_amdgcn_wave_barrier();
+        limit_frame(me[S_ETA], me[S_M], me[S_W], me[S_B], sn[0][lb], sn[1][lb], sn[2][lb], sn[0][ld], sn[1][ld],
+                    sn[2][ld], sn[3][lb], sn[4][lb], sn[5][lb], sn[3][ld], sn[4][ld], sn[5][ld], a.dx, a.idx, a.eps,
+                    a.g, Dm);
+        T o3[3];
+        limit_frame(me[S_ETA], me[S_W], me[S_M], me[S_B], ym[S_ETA], ym[S_W], ym[S_M], yp[S_ETA], yp[S_W], yp[S_M],
+                    ym[S_H2], ym[S_W2], ym[S_M2], yp[S_H2], yp[S_W2], yp[S_M2], a.dy, a.idy, a.eps, a.g, o3);
+        Dm[3] = o3[0]; Dm[4] = o3[2]; Dm[5] = o3[1];
+        __builtin_amdgcn_wave_barrier();
+      } else {
+#pragma unroll
+        for (int k = 0; k < 6; ++k) Dm[k] = me[3 + k];
+      }
+#pragma unroll
+      for (int k = 0; k < 6; ++k) L.d[row][k][lane] = Dm[k];
+    }
+  }
+  const auto fetch_update = [&](int task, T u[6], T base[3]) {
+    const int row = task / 3, third = task % 3;
+    const size_t q = (size_t)(r0 + row) * a.nx + cq;
+    u[0] = a.S[q]; u[1] = a.S[3 * n + q]; u[2] = a.S[6 * n + q];
+    u[3] = a.S[n + q]; u[4] = a.S[2 * n + q]; u[5] = a.b[q];
+    if (MODE == MODE_STAGE1 || MODE == MODE_STAGE2) {
+      const T* p = third == 0 ? a.Sn + q : a.Dn + (size_t)(3 * (third - 1)) * n + q;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) base[k] = p[k * n];
+    }
+  };
+  T u[6], base[3];
+  if (w < 3 * nr) fetch_update(w, u, base);
+  __syncthreads();
+  for (int task = w; task < 3 * nr; task += W) {
+    if (task != w) fetch_update(task, u, base);
+    const int row = task / 3, third = task % 3;
+    const size_t q = (size_t)(r0 + row) * a.nx + cq;
+    if (third == 0) small_update<T, MODE, 0>(a, L, row, q, col_out, dt, u, base, tx + r0 + row);
+    else if (third == 1) small_update<T, MODE, 1>(a, L, row, q, col_out, dt, u, base, 0);
+    else small_update<T, MODE, 2>(a, L, row, q, col_out, dt, u, base, 0);
+  }
+}
+
 // --------------------------------------------------------------------------- small kernels
 // Largest speeds of a workgroup of 256 threads into slot blockIdx.x of a set.
 template <class T>
@@ -761,6 +942,7 @@ struct swe_hweno_ctx {
   const void* g_state = nullptr;
   int g_tend = 0;
   int rows = ROWS_DEFAULT;  // rows marched per wave (2D), chosen at init
+  int small = 0;            // 2D: rows per workgroup of k_small, or 0 for marching wavefronts
   // kernel timing: event pairs around stage kernels (slot 0 = bare right-hand side, 1..3 = stages)
   bool timing = false;
   struct Pending { hipEvent_t a, b; int slot; };
@@ -812,7 +994,8 @@ template <class T> bool is_type(const swe_hweno_ctx* c) { return c->f32 == (size
 
 dim3 stage_grid(const swe_hweno_ctx* c) {
   const unsigned gx = (unsigned)((c->p.nx + OUT_COLS - 1) / OUT_COLS);
-  const unsigned gy = c->p.dim == 2 ? (unsigned)((c->p.ny + c->rows - 1) / c->rows) : 1u;
+  const int rows = c->small ? c->small : c->rows;
+  const unsigned gy = c->p.dim == 2 ? (unsigned)((c->p.ny + rows - 1) / rows) : 1u;
   return dim3(gx, gy, 1);
 }
 
@@ -839,7 +1022,7 @@ template <class T> KArgs<T> base_args(const swe_hweno_ctx* c) {
   a.dx = T(dx); a.dy = T(dy);
   a.idx = T(1.0 / dx); a.idy = T(1.0 / dy);
   a.g = T(c->p.g); a.eps = T(c->p.eps);
-  a.rows = c->rows;
+  a.rows = c->small ? c->small : c->rows;
   a.cfl = c->p.cfl; a.fdt = c->p.fixed_dt; a.cdx = dx; a.cdy = dy;
   a.fixed_dt = (c->p.flags & SWE_FIXED_DT) ? 1 : 0;
   return a;
@@ -855,6 +1038,12 @@ template <class T> void stage_speeds(const swe_hweno_ctx* c, KArgs<T>& a, int st
 }
 
 template <class T, int MODE> void launch_stage_mode(const swe_hweno_ctx* c, const KArgs<T>& a, hipStream_t s) {
+  if (c->small) {
+    const size_t lds = small_lds_words(c->small) * sizeof(T);
+    if (c->small == 1) hipLaunchKernelGGL((k_small<T, MODE, 4>), stage_grid(c), dim3(4 * WAVE), lds, s, a);
+    else hipLaunchKernelGGL((k_small<T, MODE, 8>), stage_grid(c), dim3(8 * WAVE), lds, s, a);
+    return;
+  }
   if (c->p.dim == 2) hipLaunchKernelGGL((k_stage<T, 2, MODE>), stage_grid(c), dim3(WAVE), 0, s, a);
   else hipLaunchKernelGGL((k_stage<T, 1, MODE>), stage_grid(c), dim3(WAVE), 0, s, a);
 }
@@ -981,6 +1170,30 @@ int choose_rows(int nx, int ny, int slots) {
   return best;
 }
 
+// Rows per workgroup of k_small, or 0 for marching wavefronts: the fewest for which every workgroup is resident at
+// once, one per CU, up to 8 (their LDS). With one row a workgroup has 4 wavefronts, one per SIMD, else 8. A further
+// row costs about 1.5 us, from 7.7 us at one row to 17.8 at 8; marching wavefronts take 19.3 us at their shortest marches, 22
+// where this rule ends (about 340^2), and 24 at 400^2, where two rounds of 6 rows take 28.7. In single
+// precision 6.9 to 13.3 us against 16.9. A choice of rows by the environment keeps the marching wavefronts.
+constexpr int SMALL_ROWS = 8;
+int choose_small(int nx, int ny, int cus) {
+  if (std::getenv("SWE_HWENO_ROWS")) return 0;
+  const long gx = (nx + OUT_COLS - 1) / OUT_COLS;
+  for (int r = 1; r <= SMALL_ROWS; ++r)
+    if (gx * ((ny + r - 1) / r) <= cus) return r;
+  return 0;
+}
+
+// The tile of a context on the current device.
+void choose_tile(swe_hweno_ctx* c) {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) !=
+      hipSuccess || cus <= 0)
+    cus = 256;
+  c->rows = choose_rows(c->p.nx, c->p.dim == 2 ? c->p.ny : 1, 4 * cus);
+  c->small = c->p.dim == 2 ? choose_small(c->p.nx, c->p.ny, cus) : 0;
+}
+
 int take_device_error(swe_hweno_ctx* c) {
   int e = 0;
   if (hipMemcpyAsync(&e, &c->sc->err, sizeof(int), hipMemcpyDeviceToHost, c->stream) != hipSuccess) return SWE_EHIP;
@@ -1042,13 +1255,7 @@ int init_impl(const swe_hweno_params* p, const T* b, const T* bx, const T* by, v
   c->Dn = base + at_dn;
   c->bx = (T*)c->b + c->n;
   c->by = (T*)c->b + 2 * c->n;
-  {
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) !=
-        hipSuccess || cus <= 0)
-      cus = 256;
-    c->rows = choose_rows(p->nx, p->dim == 2 ? p->ny : 1, 4 * cus);
-  }
+  choose_tile(c);
   bool ok = hipStreamCreateWithFlags(&c->cap, hipStreamNonBlocking) == hipSuccess;
   ok = ok && hipMemcpyAsync(c->b, b, plane, hipMemcpyDeviceToDevice, c->stream) == hipSuccess;
   ok = ok && hipMemcpyAsync(c->bx, bx, plane, hipMemcpyDeviceToDevice, c->stream) == hipSuccess;
@@ -1229,13 +1436,7 @@ int step_noalloc_impl(const swe_hweno_params* p, double* state, const double* b,
   c.S1 = planes;
   c.S2 = planes + (size_t)c.nf * c.n;
   c.Dn = planes + (size_t)2 * c.nf * c.n;
-  {
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) !=
-        hipSuccess || cus <= 0)
-      cus = 256;
-    c.rows = choose_rows(p->nx, p->dim == 2 ? p->ny : 1, 4 * cus);
-  }
+  choose_tile(&c);
   if (dt > 0) { c.p.flags |= SWE_FIXED_DT; c.p.fixed_dt = dt; }
   hipLaunchKernelGGL(k_setup, dim3(1), dim3(ASLOTS), 0, c.stream, c.sc, c.sp, dbits(p->alpha_x),
                      dbits(p->dim == 2 ? p->alpha_y : 0.0));
@@ -1266,7 +1467,7 @@ int swe_hweno_tile(int* cols_per_wave, int* rows_per_wave) {
 int swe_hweno_ctx_tile(const swe_hweno_ctx* c, int* cols_per_wave, int* rows_per_wave) {
   if (!c || !cols_per_wave || !rows_per_wave) return SWE_EINVAL;
   *cols_per_wave = OUT_COLS;
-  *rows_per_wave = c->rows;
+  *rows_per_wave = c->small ? c->small : c->rows;
   return SWE_OK;
 }
 
