@@ -15,9 +15,6 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
-    # a product and a sum become an FMA where one expression holds both, never across statements: then every
-    # inlined copy of a routine rounds alike, and tilings and kernels that share it give the same bits
-    "-ffp-contract=on",
     # packed FP32 forms are kept out of the generated code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-I" + os.path.join(ROOT, "include"),

@@ -8,7 +8,6 @@
 // node fluxes and their total derivatives (eqs. (3.3), (3.5)) and the limiter (Sec. 2.2). The
 // Lax-Friedrichs speed alpha is a constant here (the adjoint is taken with alpha frozen).
 #pragma once
-#include "hweno_device.hpp"
 
 namespace swe {
 

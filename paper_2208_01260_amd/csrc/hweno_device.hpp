@@ -6,10 +6,8 @@
 // the surface, the momentum normal to the interfaces of the sweep and the tangential one. The
 // y-sweep is then the x-sweep applied to (eta, w, m) with the roles of the x- and
 // y-derivatives exchanged, so one device routine serves both directions.
-#pragma once
-#include <hip/hip_runtime.h>
-
-namespace swe {
+// Included once per arithmetic type's namespace (SWE_NS), so without a guard.
+namespace SWE_NS {
 
 // Slots of a raw node record (paper variables, 2D order; 1D uses eta, m, H1=H, M1=M, b, B1=B).
 enum { S_ETA = 0, S_M, S_W, S_H1, S_M1, S_W1, S_H2, S_M2, S_W2, S_B, S_BX, S_BY, NREC };
@@ -352,4 +350,4 @@ __device__ __forceinline__ void limit_frame(T e0, T mn0, T mt0, T b0, T em, T mn
   out[2] = ut * (v1 + v3) + v2;
 }
 
-}  // namespace swe
+}  // namespace SWE_NS

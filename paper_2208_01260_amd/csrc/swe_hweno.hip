@@ -28,10 +28,9 @@
 #include <map>
 #include <mutex>
 #include <string>
+#include <type_traits>
 #include <vector>
 
-#include "hweno_adjoint.hpp"
-#include "hweno_device.hpp"
 #include "swe_hweno.h"
 
 namespace swe {
@@ -62,28 +61,6 @@ constexpr int ASET = ASLOTS * ASTRIDE;
 // alpha of U^n, U^(1), U^(2), fixed, and of a bare right-hand side. A stage reads one of the first three,
 // fills the next and clears the one before: nothing else touches that one while it runs.
 enum { SP_N = 0, SP_1, SP_2, SP_FIX, SP_RHS, SP_SETS };
-
-template <class T>
-struct KArgs {
-  const T* S;             // state whose right-hand side / stage is computed
-  const T* Sn;            // U^n at the start of the step (stages 1, 2)
-  const T* Dn;            // D^{n,mod} (stages 1, 2)
-  const T* b;
-  const T* bx;
-  const T* by;
-  T* out;                 // right-hand side, or the next stage state
-  T* Dn_out;              // stage 0: D^{n,mod}
-  const unsigned long long* a_in;  // Lax-Friedrichs speeds used
-  unsigned long long* a_out;       // max-reduction of the output state's speeds
-  unsigned long long* a_clear;     // the set this stage clears
-  const unsigned long long* a_n;   // first stage: speeds of U^n, for the CFL step
-  DevScal* sc;
-  int amask;                       // slots of the sets of speeds, less one
-  int nx, ny, bcx, bcy, limiter, rows;
-  T dx, dy, idx, idy, g, eps;
-  double cfl, fdt, cdx, cdy;       // first stage: the CFL step's parameters in double
-  int fixed_dt, use_tend;
-};
 
 // Largest finite value of the arithmetic type.
 template <class T> __device__ __forceinline__ constexpr T big_value();
@@ -122,141 +99,11 @@ __device__ __forceinline__ __attribute__((address_space(1))) T* opq(T* p) {
   return g;
 }
 
-// Raw node record at (i, j) in the slots of hweno_device.hpp, ghost values by parity:
-// across an x-wall m, H1, W1, M2, B1 are odd; across a y-wall w, W1, H2, M2, B2 are odd.
-template <int DIM, class T>
-__device__ __forceinline__ void load_raw(const KArgs<T>& a, const T* __restrict__ S, int i, int j, T r[NREC],
-                                         bool& rx, bool& ry) {
-  ry = false;
-  const int ii = fold(i, a.nx, a.bcx, rx);
-  const int jj = DIM == 2 ? fold(j, a.ny, a.bcy, ry) : 0;
-  const size_t n = (size_t)a.nx * (DIM == 2 ? a.ny : 1);
-  const size_t q = (size_t)jj * a.nx + ii;
-  if (DIM == 2) {
-    auto p = opq(S + q);
-#pragma unroll
-    for (int f = 0; f < 9; ++f) {
-      r[f] = *p;
-      if (f < 8) p = opq(p + n);
-    }
-    r[S_B] = *opq(a.b + q); r[S_BX] = *opq(a.bx + q); r[S_BY] = *opq(a.by + q);
-  } else {
-    r[S_ETA] = S[q]; r[S_M] = S[n + q]; r[S_W] = T(0.0);
-    r[S_H1] = S[2 * n + q]; r[S_M1] = S[3 * n + q]; r[S_W1] = T(0.0);
-    r[S_H2] = T(0.0); r[S_M2] = T(0.0); r[S_W2] = T(0.0);
-    r[S_B] = a.b[q]; r[S_BX] = a.bx[q]; r[S_BY] = T(0.0);
-  }
-}
-
-// The ghost parities of a record read across an x-wall (rx) or a y-wall (ry).
-template <class T>
-__device__ __forceinline__ void apply_flips(T r[NREC], bool rx, bool ry) {
-  if (rx) { r[S_M] = -r[S_M]; r[S_H1] = -r[S_H1]; r[S_W1] = -r[S_W1]; r[S_M2] = -r[S_M2]; r[S_BX] = -r[S_BX]; }
-  if (ry) { r[S_W] = -r[S_W]; r[S_W1] = -r[S_W1]; r[S_H2] = -r[S_H2]; r[S_M2] = -r[S_M2]; r[S_BY] = -r[S_BY]; }
-}
-
-template <int DIM, class T>
-__device__ __forceinline__ void load_rec(const KArgs<T>& a, const T* __restrict__ S, int i, int j, T r[NREC]) {
-  bool rx, ry;
-  load_raw<DIM>(a, S, i, j, r, rx, ry);
-  apply_flips(r, rx, ry);
-}
-
-// Node fluxes through LDS: slot k of a NodeF at lane l is sn[k][l].
-constexpr int NNODE = 18;
-template <class T>
-__device__ __forceinline__ void nodef_store(T (*sn)[64], int l, const NodeF<T>& X) {
-  const T v[NNODE] = {X.e, X.mn, X.mt, X.d0, X.d1, X.d2, X.f0, X.f1, X.f2,
-                           X.p0, X.p1, X.p2, X.q0, X.q1, X.q2, X.b, X.bn, X.bt};
-#pragma unroll
-  for (int k = 0; k < NNODE; ++k) sn[k][l] = v[k];
-}
-template <class T>
-__device__ __forceinline__ void nodef_load(T (*sn)[64], int l, NodeF<T>& X) {
-  X.e = sn[0][l]; X.mn = sn[1][l]; X.mt = sn[2][l]; X.d0 = sn[3][l]; X.d1 = sn[4][l]; X.d2 = sn[5][l];
-  X.f0 = sn[6][l]; X.f1 = sn[7][l]; X.f2 = sn[8][l]; X.p0 = sn[9][l]; X.p1 = sn[10][l]; X.p2 = sn[11][l];
-  X.q0 = sn[12][l]; X.q1 = sn[13][l]; X.q2 = sn[14][l]; X.b = sn[15][l]; X.bn = sn[16][l]; X.bt = sn[17][l];
-}
-
-// y-frame node fluxes kept per row: the six values of a NodeF that are not raw record slots
-// (F1, F2, P1, P2, Q1, Q2), in a ring of four rows of the march (own lane only).
-template <class T>
-__device__ __forceinline__ void yring_store(T (*ring)[6][WAVE], int row, int lane, const T* __restrict__ r, T g) {
-  NodeF<T> X;
-  node_frame<1>(r, g, X);
-  const int s = row & 3;
-  ring[s][0][lane] = X.f1; ring[s][1][lane] = X.f2;
-  ring[s][2][lane] = X.p1; ring[s][3][lane] = X.p2;
-  ring[s][4][lane] = X.q1; ring[s][5][lane] = X.q2;
-}
-template <class T>
-__device__ __forceinline__ void yring_load(T (*ring)[6][WAVE], int row, int lane, const T* __restrict__ r,
-                                           NodeF<T>& X) {
-  const int s = row & 3;
-  X.e = r[S_ETA]; X.mn = r[S_W]; X.mt = r[S_M];
-  X.d0 = r[S_H2]; X.d1 = r[S_W2]; X.d2 = r[S_M2];
-  X.f0 = X.mn; X.f1 = ring[s][0][lane]; X.f2 = ring[s][1][lane];
-  X.p0 = X.d1; X.p1 = ring[s][2][lane]; X.p2 = ring[s][3][lane];
-  X.q0 = r[S_W1]; X.q1 = ring[s][4][lane]; X.q2 = ring[s][5][lane];
-  X.b = r[S_B]; X.bn = r[S_BY]; X.bt = r[S_BX];
-}
-
-template <class T>
-__device__ __forceinline__ void ifo_to_array(const IfO<T>& o, T* v) {
-  v[0] = o.F0; v[1] = o.F1; v[2] = o.F2; v[3] = o.B0; v[4] = o.B1; v[5] = o.B2; v[6] = o.P0;
-  v[7] = o.P1; v[8] = o.P2; v[9] = o.PB; v[10] = o.M0; v[11] = o.M1; v[12] = o.M2; v[13] = o.MB;
-}
-
-// Add the contribution of one sweep (left/right interfaces l, r, spacing id = 1/dx) to the
-// 9 right-hand-side slots R (2D order eta, m, w, H1, M1, W1, H2, M2, W2). un/ut/dn/dt are the
-// slots of the frame's normal and tangential momentum and derivative triples.
-template <int DIR, class T>
-__device__ __forceinline__ void assemble(const T* l, const T* r, T eta, T H1, T H2,
-                                         T g, T id, T R[9]) {
-  const int un = DIR == 0 ? 1 : 2, ut = DIR == 0 ? 2 : 1;
-  const int dn = DIR == 0 ? 3 : 6, dt = DIR == 0 ? 6 : 3;  // first slot of D_n, D_t
-  const T Hn = DIR == 0 ? H1 : H2, Ht = DIR == 0 ? H2 : H1;
-  const T db0 = r[3] - l[3], db1 = r[4] - l[4], db2 = r[5] - l[5];
-  const T ge = g * eta;
-  R[0] -= ((r[0] - l[0]) + ge * db0) * id;
-  R[un] -= ((r[1] - l[1]) + ge * db1) * id;
-  R[ut] -= ((r[2] - l[2]) + ge * db2) * id;
-  const T gn = g * Hn, gt = g * Ht;
-  R[dn + 0] -= ((r[6] - l[6]) + gn * db0) * id;
-  R[dn + un] -= ((r[7] - l[7]) + gn * db1 + ge * (r[9] - l[9])) * id;
-  R[dn + ut] -= ((r[8] - l[8]) + gn * db2) * id;
-  R[dt + 0] -= ((r[10] - l[10]) + gt * db0) * id;
-  R[dt + un] -= ((r[11] - l[11]) + gt * db1 + ge * (r[13] - l[13])) * id;
-  R[dt + ut] -= ((r[12] - l[12]) + gt * db2) * id;
-}
-
 template <class T>
 __device__ __forceinline__ T wave_max(T v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, WAVE));
   return v;
-}
-
-// x / 3 rounded to nearest: the product with the rounded 1/3, corrected by one FMA step on the
-// exact remainder (equal to the IEEE quotient; checked against it on 2e8 random doubles).
-template <class T>
-__device__ __forceinline__ T div3(T x) {
-  const T y = T(1.0 / 3.0);
-  const T q = x * y;
-  return fma(fma(T(-3.0), q, x), y, q);
-}
-
-// Speeds |u| + c, |v| + c of a node for the next Lax-Friedrichs split; flags dry / non-finite.
-template <class T>
-__device__ __forceinline__ void speeds(T e, T m, T w, T b, T g, T& ax, T& ay,
-                                       int& err) {
-  const T h = e - b;
-  if (!(h > T(0.0))) { err |= (h == h) ? ERR_DRY : ERR_NONFINITE; return; }
-  const T c = sqrt_pos(g * h), ih = rcp(h);
-  const T sx = fabs(m * ih) + c, sy = fabs(w * ih) + c;
-  if (!(sx <= big_value<T>()) || !(sy <= big_value<T>())) { err |= ERR_NONFINITE; return; }
-  ax = fmax(ax, sx);
-  ay = fmax(ay, sy);
 }
 
 // The two speeds of a set (all 64 lanes of a wavefront take part), in scalar registers. A grid of few
@@ -278,293 +125,6 @@ __device__ __forceinline__ void read_speeds(const unsigned long long* __restrict
   ay = uniform(wave_max(bits2d(q[1])));
 }
 
-// Time step of a stage's wavefront; false if the step does nothing. Every wavefront of the first stage forms it
-// for itself from the speeds of U^n (the CFL step or a fixed one, clipped at t_end), and the first tile's
-// leaves it for the other stages, instead of a one-thread kernel in front of the stages, which costs 4.5 us
-// on this device whatever it does. What the first stage decides by (t, t_end, the speeds of U^n and, in a batch, the
-// error flag) is written only by the other stages: the clock and the cleared set by the second stage, and a
-// batch's first stage flags errors in err0, which the second stage folds into err.
-template <class T, int DIM, int MODE, bool BATCH>
-__device__ __forceinline__ bool step_start(const KArgs<T>& a, bool first_tile, double sax, double say, double& dt) {
-  const int lane = (int)(threadIdx.x & (WAVE - 1));
-  DevScal* s = a.sc;
-  if (MODE == MODE_STAGE0) {
-    if (a.fixed_dt) {
-      dt = a.fdt;
-    } else {
-      if (a.a_n != a.a_in) read_speeds(a.a_n, a.amask, sax, say);
-      dt = uniform(cfl_step(DIM, a.cfl, sax, say, a.cdx, a.cdy));
-    }
-    bool active = true, bad = false;
-    if (a.use_tend) {
-      const double t = s->t, t_end = s->t_end;
-      if (!(t < t_end)) { active = false; dt = 0.0; }
-      else if (t + dt > t_end) dt = t_end - t;
-    }
-    if (BATCH && s->err) {  // the last step met a dry or non-finite node: this instance stops
-      active = false;
-      dt = 0.0;
-    } else if (!(dt > 0.0) || !(dt <= DBL_MAX)) {
-      bad = active;
-      active = false;
-    }
-    if (first_tile && lane == 0) {
-      s->dt = dt;
-      s->active = active ? 1 : 0;
-      if (bad) atomicOr(BATCH ? &s->err0 : &s->err, ERR_NONFINITE);
-    }
-    if (!active) return false;
-  } else {
-    if (BATCH && MODE == MODE_STAGE1 && first_tile && lane == 0 && s->err0) {
-      atomicOr(&s->err, s->err0);
-      s->err0 = 0;
-    }
-    if (s->active == 0) return false;
-    dt = s->dt;
-    if (MODE == MODE_STAGE1 && first_tile && lane == 0) { s->t += dt; s->steps += 1; }
-  }
-  if (first_tile && lane <= a.amask) {
-    unsigned long long* q = a.a_clear + (size_t)lane * ASTRIDE;
-    q[0] = q[1] = 0ull;
-  }
-  return true;
-}
-
-template <class T>
-__device__ __forceinline__ void flush_speeds(const KArgs<T>& a, int* errp, int slot, T ax, T ay, int err) {
-  ax = wave_max(ax);
-  ay = wave_max(ay);
-  int e = err;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) e |= __shfl_xor(e, o, WAVE);
-  if ((threadIdx.x & (WAVE - 1)) == 0) {
-    unsigned long long* o = a.a_out + (size_t)(slot & a.amask) * ASTRIDE;
-    atomicMax(&o[0], (unsigned long long)__double_as_longlong((double)ax));
-    atomicMax(&o[1], (unsigned long long)__double_as_longlong((double)ay));
-    if (e) atomicOr(errp, e);
-  }
-}
-
-// --------------------------------------------------------------------------- the fused stage
-// One wavefront's tile: output columns [tx*60, tx*60+60) of rows [ty*rows, ty*rows+rows).
-template <class T, int DIM, int MODE, bool BATCH>
-__device__ __forceinline__ void stage_tile(const KArgs<T>& a, int tx, int ty) {
-  __shared__ T sn[NNODE][WAVE];  // x-frame fluxes of the current row, one node per lane
-  __shared__ T sf[14][WAVE];     // x-interface quantities (lane l: interface left of its column)
-  __shared__ T sy[14][WAVE];     // y-interface quantities of the previous row (own lane)
-  __shared__ T syf[4][6][WAVE];  // y-frame fluxes of rows r-1 .. r+2 (own lane)
-  const int lane = threadIdx.x;
-  const int c = tx * OUT_COLS - 2 + lane;  // this lane's column
-  const int r0 = DIM == 2 ? ty * a.rows : 0;
-  const int r1 = DIM == 2 ? min(r0 + a.rows, a.ny) : 1;
-  const bool col_out = lane >= 2 && lane < WAVE - 2 && c < a.nx;
-  const int cq = col_out ? c : 0;  // a column that is always inside the grid
-  const size_t n = (size_t)a.nx * (DIM == 2 ? a.ny : 1);
-  const int nu = DIM == 2 ? 3 : 2, nd = DIM == 2 ? 6 : 2;
-  const int la = max(lane - 2, 0), lb = max(lane - 1, 0), ld = min(lane + 1, WAVE - 1);
-  T amx = T(0.0), amy = T(0.0);
-  int err = 0;
-
-  // y window: raw records of rows r-1, r, r+1 (2D); the flux of interface r-1/2 waits in sy
-  T wm2[NREC], wm1[NREC], w0[NREC], wp1[NREC];
-  load_rec<DIM>(a, a.S, c, r0, w0);
-  if (DIM == 2) {
-    load_rec<DIM>(a, a.S, c, r0 - 2, wm2);
-    load_rec<DIM>(a, a.S, c, r0 - 1, wm1);
-    load_rec<DIM>(a, a.S, c, r0 + 1, wp1);
-  }
-  // the speeds and the step's scalars arrive while the window does
-  double sax, say, dtd = 0.0;
-  read_speeds(a.a_in, a.amask, sax, say);
-  if (MODE != MODE_RHS && !step_start<T, DIM, MODE, BATCH>(a, tx == 0 && ty == 0, sax, say, dtd)) return;
-  const T axl = T(sax), ayl = T(say), dt = T(dtd);
-  if (DIM == 2) {
-    yring_store(syf, r0 - 2, lane, wm2, a.g);
-    yring_store(syf, r0 - 1, lane, wm1, a.g);
-    yring_store(syf, r0, lane, w0, a.g);
-    yring_store(syf, r0 + 1, lane, wp1, a.g);
-    IfO<T> o;
-    auto fy = [&](int k, NodeF<T>& X) {
-      yring_load(syf, r0 - 2 + k, lane, k == 0 ? wm2 : (k == 1 ? wm1 : (k == 2 ? w0 : wp1)), X);
-    };
-    interface_flux(fy, ayl, a.dy, a.eps, a.g, o);
-    T v[14];
-    ifo_to_array(o, v);
-#pragma unroll
-    for (int k = 0; k < 14; ++k) sy[k][lane] = v[k];
-  }
-
-  for (int r = r0; r < r1; ++r) {
-    const size_t q = (size_t)r * a.nx + cq;
-    // loads whose latency the x-sweep hides: the next row of the window, U^n and D^{n,mod}. The new
-    // row's ghost parities are applied where the y-sweep first reads it, so that no instruction
-    // before that point depends on these loads.
-    T wp2[NREC];
-    bool f2x = false, f2y = false;
-    if (DIM == 2) load_raw<DIM>(a, a.S, c, r + 2, wp2, f2x, f2y);
-    T un_[3], dn_[6];
-    if (MODE == MODE_STAGE1 || MODE == MODE_STAGE2) {
-      auto pS = opq(a.Sn + q);
-      auto pD = opq(a.Dn + q);
-#pragma unroll
-      for (int k = 0; k < 3; ++k) if (k < nu) { un_[k] = *pS; pS = opq(pS + n); }
-#pragma unroll
-      for (int k = 0; k < 6; ++k) if (k < nd) { dn_[k] = *pD; pD = opq(pD + n); }
-    }
-    T R[9];
-#pragma unroll
-    for (int k = 0; k < 9; ++k) R[k] = T(0.0);
-    const T eta = w0[S_ETA], H1 = w0[S_H1], H2 = w0[S_H2];
-
-    // x-sweep of row r: each lane's x-frame fluxes are computed once and shared through LDS
-    __syncthreads();  // the previous row's readers of sn and sf are done
-    {
-      NodeF<T> me;
-      node_frame<0>(w0, a.g, me);
-      nodef_store(sn, lane, me);
-      __syncthreads();
-      IfO<T> o;
-      auto fx = [&](int k, NodeF<T>& X) {
-        if (k == 2) X = me;
-        else nodef_load(sn, k == 0 ? la : (k == 1 ? lb : ld), X);
-      };
-      interface_flux(fx, axl, a.dx, a.eps, a.g, o);
-      T xl[14];
-      ifo_to_array(o, xl);
-#pragma unroll
-      for (int k = 0; k < 14; ++k) sf[k][lane] = xl[k];
-      __syncthreads();
-      T xr[14];
-#pragma unroll
-      for (int k = 0; k < 14; ++k) xr[k] = sf[k][ld];
-      assemble<0>(xl, xr, eta, H1, H2, a.g, a.idx, R);
-    }
-    // y-sweep: interface r+1/2 from rows r-1 .. r+2
-    if (DIM == 2) {
-      IfO<T> o;
-      apply_flips(wp2, f2x, f2y);
-      yring_store(syf, r + 2, lane, wp2, a.g);
-      auto fy = [&](int k, NodeF<T>& X) {
-        yring_load(syf, r - 1 + k, lane, k == 0 ? wm1 : (k == 1 ? w0 : (k == 2 ? wp1 : wp2)), X);
-      };
-      interface_flux(fy, ayl, a.dy, a.eps, a.g, o);
-      T ynew[14], yprev[14];
-      ifo_to_array(o, ynew);
-#pragma unroll
-      for (int k = 0; k < 14; ++k) { yprev[k] = sy[k][lane]; sy[k][lane] = ynew[k]; }
-      assemble<1>(yprev, ynew, eta, H1, H2, a.g, a.idy, R);
-    }
-
-    if (MODE == MODE_RHS) {
-      if (col_out) {
-        if (DIM == 2) {
-          auto po = opq(a.out + q);
-#pragma unroll
-          for (int k = 0; k < 9; ++k) {
-            *po = R[k];
-            if (k < 8) po = opq(po + n);
-          }
-        } else {
-          a.out[q] = R[0]; a.out[n + q] = R[1]; a.out[2 * n + q] = R[3]; a.out[3 * n + q] = R[4];
-        }
-        // the node's depth must be positive and the result finite (a product with 0 is NaN
-        // exactly for a non-finite value)
-        const T h = w0[S_ETA] - w0[S_B];
-        T z = T(0.0);
-#pragma unroll
-        for (int k = 0; k < 9; ++k) z = fma(R[k], T(0.0), z);
-        if (!(h > T(0.0))) err |= (h == h) ? ERR_DRY : ERR_NONFINITE;
-        if (z != z) err |= ERR_NONFINITE;
-      }
-    } else if (MODE != MODE_STAGE1 || col_out) {
-        // limited derivatives of this stage's state at the node (Sec. 2.2); the x-neighbours'
-        // surface, momenta and x-derivatives are the first six slots of their shared fluxes.
-        // The first and third stages run the limiter and the update on every lane and mask only
-        // the stores and the speed reduction, which leaves the compiler free to schedule them
-        // across the row; the second stage keeps them under the branch (each form is the faster
-        // one for its stage on this device; the results are the same bits either way).
-        T Dm[6];
-        if (a.limiter) {
-          limit_frame(w0[S_ETA], w0[S_M], w0[S_W], w0[S_B], sn[0][lb], sn[1][lb], sn[2][lb], sn[0][ld], sn[1][ld],
-                      sn[2][ld], sn[3][lb], sn[4][lb], sn[5][lb], sn[3][ld], sn[4][ld], sn[5][ld], a.dx, a.idx,
-                      a.eps, a.g, Dm);
-          if (DIM == 2) {
-            T o3[3];
-            limit_frame(w0[S_ETA], w0[S_W], w0[S_M], w0[S_B], wm1[S_ETA], wm1[S_W], wm1[S_M], wp1[S_ETA],
-                        wp1[S_W], wp1[S_M], wm1[S_H2], wm1[S_W2], wm1[S_M2], wp1[S_H2], wp1[S_W2], wp1[S_M2], a.dy,
-                        a.idy, a.eps, a.g, o3);
-            Dm[3] = o3[0]; Dm[4] = o3[2]; Dm[5] = o3[1];
-          }
-        } else {
-          Dm[0] = w0[S_H1]; Dm[1] = w0[S_M1]; Dm[2] = w0[S_W1];
-          Dm[3] = w0[S_H2]; Dm[4] = w0[S_M2]; Dm[5] = w0[S_W2];
-        }
-        // SSP-RK3 combination (eq. (2.11)), written over a common denominator
-        const int uslot[3] = {S_ETA, S_M, S_W};
-        const int rd[6] = {3, 4, 5, 6, 7, 8};
-        T Unew[3] = {T(0.0), T(0.0), T(0.0)};
-        T vout[9];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          if (k >= nu) break;
-          const T u = w0[uslot[k]] + dt * R[k];
-          T v;
-          if (MODE == MODE_STAGE0) v = u;
-          else if (MODE == MODE_STAGE1) v = (T(3.0) * un_[k] + u) * T(0.25);
-          else v = div3(un_[k] + T(2.0) * u);
-          Unew[k] = v;
-          vout[k] = v;
-        }
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-          if (k >= nd) break;
-          const T u = Dm[k] + dt * R[rd[k]];
-          T v;
-          if (MODE == MODE_STAGE0) {
-            v = u;
-          } else if (MODE == MODE_STAGE1) {
-            v = (T(3.0) * dn_[k] + u) * T(0.25);
-          } else {
-            v = div3(dn_[k] + T(2.0) * u);
-          }
-          vout[nu + k] = v;
-        }
-        // only the interior columns store and reduce their speeds
-        if (col_out) {
-          auto po = opq(a.out + q);
-#pragma unroll
-          for (int k = 0; k < 9; ++k) {
-            if (k >= nu + nd) break;
-            *po = vout[k];
-            po = opq(po + n);
-          }
-          if (MODE == MODE_STAGE0) {
-            auto pdo = opq(a.Dn_out + q);
-#pragma unroll
-            for (int k = 0; k < 6; ++k) {
-              if (k >= nd) break;
-              *pdo = Dm[k];
-              pdo = opq(pdo + n);
-            }
-          }
-          speeds(Unew[0], Unew[1], Unew[2], w0[S_B], a.g, amx, amy, err);
-        }
-    }
-    if (DIM == 2) {
-#pragma unroll
-      for (int k = 0; k < NREC; ++k) { wm1[k] = w0[k]; w0[k] = wp1[k]; wp1[k] = wp2[k]; }
-    }
-  }
-  if (MODE != MODE_RHS) {
-    flush_speeds(a, BATCH && MODE == MODE_STAGE0 ? &a.sc->err0 : &a.sc->err, tx + ty, amx, amy, err);
-  } else {
-    int e = err;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) e |= __shfl_xor(e, o, WAVE);
-    if (threadIdx.x == 0 && e) atomicOr(&a.sc->err, e);
-  }
-}
-
 // Workgroups are handed to the 8 XCDs of the device round-robin by linear id. band_tile maps
 // the linear id i < n of a workgroup to a tile index so that each XCD receives a contiguous
 // band of tiles: neighbouring tiles, which read each other's halo columns and rows, then meet
@@ -574,231 +134,6 @@ constexpr unsigned NXCD = 8;
 __host__ __device__ __forceinline__ unsigned band_tile(unsigned i, unsigned n) {
   const unsigned x = i % NXCD, k = i / NXCD, q = n / NXCD, rm = n % NXCD;
   return x * q + (x < rm ? x : rm) + k;
-}
-
-template <class T, int DIM, int MODE>
-__global__ __launch_bounds__(WAVE) void k_stage(KArgs<T> a) {
-  const unsigned gx = gridDim.x;
-  const unsigned t = band_tile(blockIdx.x + blockIdx.y * gx, gx * gridDim.y);
-  stage_tile<T, DIM, MODE, false>(a, (int)(t % gx), (int)(t / gx));
-}
-
-// --------------------------------------------------------------------------- the fused stage, small grids
-// The same stage for grids that cannot fill the GPU with marching wavefronts, where a stage takes as long as one
-// wavefront's serial work. A workgroup of W wavefronts takes 60 columns by R rows, shared out as tasks of one
-// wavefront each: the R + 1 y-interfaces of a row of columns (from four rows that the wavefront loads), the R rows' x-interfaces
-// and the R rows' limiters; the quantities meet in LDS and the rows are assembled and updated by thirds
-// (U, U_x, U_y). Bound by latency: launch, one trip for the rows, then the tasks, two wavefronts per SIMD at 8
-// wavefronts. A stage in FP64, against marching wavefronts: 61 x 47 7.7 us (R = 1, W = 4) against 19.3, 200 x 100 9.0
-// (R = 2) against 19.3, 256^2 15.3 (R = 6) against 20.3, 300^2 15.9 (R = 6) against 21.0.
-template <class T>
-struct SmallLds {
-  T (*x)[NNODE][WAVE];  // [R] x-frame fluxes of a row while its wavefront works, then the x-interface left of each column
-  T (*y)[14][WAVE];     // [R + 1] y-interface below row r
-  T (*d)[6][WAVE];      // [R] the limiter's neighbour values, then the limited derivatives
-};
-constexpr size_t small_lds_words(int R) { return (size_t)WAVE * (R * NNODE + (R + 1) * 14 + R * 6); }
-
-// Planes 3 THIRD .. 3 THIRD + 2 of one row: assembly, Runge-Kutta combination and stores. u, un, dn: the node's own state
-// (eta, H1, H2, m, w, b) and the values of U^n or D^{n,mod} for these planes, loaded before the interfaces were ready.
-template <class T, int MODE, int THIRD>
-__device__ __forceinline__ void small_update(const KArgs<T>& a, const SmallLds<T>& L, int row, size_t q, bool out, T dt,
-                                             const T u[6], const T base[3], int slot) {
-  const int lane = (int)(threadIdx.x & (WAVE - 1)), ld = min(lane + 1, WAVE - 1);
-  const size_t n = (size_t)a.nx * a.ny;
-  T xl[14], xr[14], yl[14], yr[14], Rv[9];
-#pragma unroll
-  for (int k = 0; k < 14; ++k) {
-    xl[k] = L.x[row][k][lane]; xr[k] = L.x[row][k][ld];
-    yl[k] = L.y[row][k][lane]; yr[k] = L.y[row + 1][k][lane];
-  }
-#pragma unroll
-  for (int k = 0; k < 9; ++k) Rv[k] = T(0.0);
-  assemble<0>(xl, xr, u[0], u[1], u[2], a.g, a.idx, Rv);
-  assemble<1>(yl, yr, u[0], u[1], u[2], a.g, a.idy, Rv);
-  T amx = T(0.0), amy = T(0.0);
-  int err = 0;
-  if (MODE == MODE_RHS) {
-    if (out) {
-      T z = T(0.0);
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        a.out[(3 * THIRD + k) * n + q] = Rv[3 * THIRD + k];
-        z = fma(Rv[3 * THIRD + k], T(0.0), z);
-      }
-      if (THIRD == 0) {
-        const T h = u[0] - u[5];
-        if (!(h > T(0.0))) err |= (h == h) ? ERR_DRY : ERR_NONFINITE;
-      }
-      if (z != z) err |= ERR_NONFINITE;
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) err |= __shfl_xor(err, o, WAVE);
-    if (lane == 0 && err) atomicOr(&a.sc->err, err);
-    return;
-  }
-  T v[3];
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    const T s0 = THIRD == 0 ? (k == 0 ? u[0] : (k == 1 ? u[3] : u[4])) : L.d[row][3 * (THIRD - 1) + k][lane];
-    const T s = s0 + dt * Rv[3 * THIRD + k];
-    if (MODE == MODE_STAGE0) v[k] = s;
-    else if (MODE == MODE_STAGE1) v[k] = (T(3.0) * base[k] + s) * T(0.25);
-    else v[k] = div3(base[k] + T(2.0) * s);
-    if (out) {
-      a.out[(3 * THIRD + k) * n + q] = v[k];
-      if (MODE == MODE_STAGE0 && THIRD > 0) a.Dn_out[(3 * (THIRD - 1) + k) * n + q] = s0;
-    }
-  }
-  if (THIRD == 0) {
-    if (out) speeds(v[0], v[1], v[2], u[5], a.g, amx, amy, err);
-    flush_speeds(a, &a.sc->err, slot, amx, amy, err);
-  }
-}
-
-template <class T, int MODE, int W>
-__global__ __launch_bounds__(W * WAVE) void k_small(KArgs<T> a) {
-  extern __shared__ __align__(16) unsigned char small_lds[];
-  const int R = a.rows;
-  SmallLds<T> L;
-  L.x = (T (*)[NNODE][WAVE])small_lds;
-  L.y = (T (*)[14][WAVE])(L.x + R);
-  L.d = (T (*)[6][WAVE])(L.y + R + 1);
-  const unsigned gx = gridDim.x;
-  const unsigned tile = band_tile(blockIdx.x + blockIdx.y * gx, gx * gridDim.y);
-  const int tx = (int)(tile % gx), ty = (int)(tile / gx);
-  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
-  const int lane = (int)(threadIdx.x & (WAVE - 1));
-  const int c = tx * OUT_COLS - 2 + lane;
-  const int r0 = ty * R, nr = min(R, a.ny - r0);
-  const bool col_out = lane >= 2 && lane < WAVE - 2 && c < a.nx;
-  const int cq = col_out ? c : 0;
-  const size_t n = (size_t)a.nx * a.ny;
-  const int la = max(lane - 2, 0), lb = max(lane - 1, 0), ld = min(lane + 1, WAVE - 1);
-  double sax, say, dtd = 0.0;
-  read_speeds(a.a_in, a.amask, sax, say);
-  if (MODE != MODE_RHS && !step_start<T, 2, MODE, false>(a, tx == 0 && ty == 0 && w == 0, sax, say, dtd)) return;
-  const T axl = T(sax), ayl = T(say), dt = T(dtd);
-  const int ntask = 2 * nr + 1 + (MODE == MODE_RHS ? 0 : nr);
-  for (int task = w; task < ntask; task += W) {
-    if (task <= nr) {  // y-interface below row r0 + task
-      T r4[4][NREC];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) load_rec<2>(a, a.S, c, r0 + task - 2 + k, r4[k]);
-      IfO<T> o;
-      auto fy = [&](int k, NodeF<T>& X) { node_frame<1>(r4[k], a.g, X); };
-      interface_flux(fy, ayl, a.dy, a.eps, a.g, o);
-      T v[14];
-      ifo_to_array(o, v);
-#pragma unroll
-      for (int k = 0; k < 14; ++k) L.y[task][k][lane] = v[k];
-    } else if (task <= 2 * nr) {  // x-interfaces of a row
-      const int row = task - nr - 1;
-      T r1[NREC];
-      load_rec<2>(a, a.S, c, r0 + row, r1);
-      NodeF<T> me;
-      node_frame<0>(r1, a.g, me);
-      nodef_store(L.x[row], lane, me);
-      __builtin_amdgcn_wave_barrier();
-      IfO<T> o;
-      auto fx = [&](int k, NodeF<T>& X) {
-        if (k == 2) X = me;
-        else nodef_load(L.x[row], k == 0 ? la : (k == 1 ? lb : ld), X);
-      };
-      interface_flux(fx, axl, a.dx, a.eps, a.g, o);
-      T v[14];
-      ifo_to_array(o, v);
-      __builtin_amdgcn_wave_barrier();
-#pragma unroll
-      for (int k = 0; k < 14; ++k) L.x[row][k][lane] = v[k];
-    } else {  // limited derivatives of a row
-      const int row = task - 2 * nr - 1;
-      T me[NREC];
-      load_rec<2>(a, a.S, c, r0 + row, me);
-      T Dm[6];
-      if (a.limiter) {
-        T ym[NREC], yp[NREC];
-        load_rec<2>(a, a.S, c, r0 + row - 1, ym);
-        load_rec<2>(a, a.S, c, r0 + row + 1, yp);
-        T (*sn)[WAVE] = L.d[row];
-#pragma unroll
-        for (int k = 0; k < 6; ++k) sn[k][lane] = me[k];  // eta, m, w, H1, M1, W1
-        __builtin_amdgcn_wave_barrier();
-        limit_frame(me[S_ETA], me[S_M], me[S_W], me[S_B], sn[0][lb], sn[1][lb], sn[2][lb], sn[0][ld], sn[1][ld],
-                    sn[2][ld], sn[3][lb], sn[4][lb], sn[5][lb], sn[3][ld], sn[4][ld], sn[5][ld], a.dx, a.idx, a.eps,
-                    a.g, Dm);
-        T o3[3];
-        limit_frame(me[S_ETA], me[S_W], me[S_M], me[S_B], ym[S_ETA], ym[S_W], ym[S_M], yp[S_ETA], yp[S_W], yp[S_M],
-                    ym[S_H2], ym[S_W2], ym[S_M2], yp[S_H2], yp[S_W2], yp[S_M2], a.dy, a.idy, a.eps, a.g, o3);
-        Dm[3] = o3[0]; Dm[4] = o3[2]; Dm[5] = o3[1];
-        __builtin_amdgcn_wave_barrier();
-      } else {
-#pragma unroll
-        for (int k = 0; k < 6; ++k) Dm[k] = me[3 + k];
-      }
-#pragma unroll
-      for (int k = 0; k < 6; ++k) L.d[row][k][lane] = Dm[k];
-    }
-  }
-  const auto fetch_update = [&](int task, T u[6], T base[3]) {
-    const int row = task / 3, third = task % 3;
-    const size_t q = (size_t)(r0 + row) * a.nx + cq;
-    u[0] = a.S[q]; u[1] = a.S[3 * n + q]; u[2] = a.S[6 * n + q];
-    u[3] = a.S[n + q]; u[4] = a.S[2 * n + q]; u[5] = a.b[q];
-    if (MODE == MODE_STAGE1 || MODE == MODE_STAGE2) {
-      const T* p = third == 0 ? a.Sn + q : a.Dn + (size_t)(3 * (third - 1)) * n + q;
-#pragma unroll
-      for (int k = 0; k < 3; ++k) base[k] = p[k * n];
-    }
-  };
-  T u[6], base[3];
-  if (w < 3 * nr) fetch_update(w, u, base);
-  __syncthreads();
-  for (int task = w; task < 3 * nr; task += W) {
-    if (task != w) fetch_update(task, u, base);
-    const int row = task / 3, third = task % 3;
-    const size_t q = (size_t)(r0 + row) * a.nx + cq;
-    if (third == 0) small_update<T, MODE, 0>(a, L, row, q, col_out, dt, u, base, tx + r0 + row);
-    else if (third == 1) small_update<T, MODE, 1>(a, L, row, q, col_out, dt, u, base, 0);
-    else small_update<T, MODE, 2>(a, L, row, q, col_out, dt, u, base, 0);
-  }
-}
-
-// --------------------------------------------------------------------------- small kernels
-// Largest speeds of a workgroup of 256 threads into slot blockIdx.x of a set.
-template <class T>
-__device__ __forceinline__ void block_speeds(T ax, T ay, int err, unsigned long long* out, int amask, int* errp) {
-  __shared__ double sx[4], sy[4];
-  __shared__ int se[4];
-  ax = wave_max(ax);
-  ay = wave_max(ay);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) err |= __shfl_xor(err, o, WAVE);
-  if ((threadIdx.x & (WAVE - 1)) == 0) {
-    const int w = (int)(threadIdx.x / WAVE);
-    sx[w] = (double)ax; sy[w] = (double)ay; se[w] = err;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const double mx = fmax(fmax(sx[0], sx[1]), fmax(sx[2], sx[3])), my = fmax(fmax(sy[0], sy[1]), fmax(sy[2], sy[3]));
-    const int e = (se[0] | se[1]) | (se[2] | se[3]);
-    unsigned long long* o = out + (size_t)((int)blockIdx.x & amask) * ASTRIDE;
-    atomicMax(&o[0], (unsigned long long)__double_as_longlong(mx));
-    atomicMax(&o[1], (unsigned long long)__double_as_longlong(my));
-    if (e) atomicOr(errp, e);
-  }
-}
-
-// Lax-Friedrichs speeds of a state (grid-stride), max-reduced into a set. Bound by its reads (b and the
-// first three planes).
-template <class T, int DIM>
-__global__ __launch_bounds__(256) void k_alpha(const T* __restrict__ S, const T* __restrict__ b, size_t n,
-                                               T g, unsigned long long* out, int amask, int* errp) {
-  T ax = T(0.0), ay = T(0.0);
-  int err = 0;
-  for (size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x; q < n; q += (size_t)gridDim.x * blockDim.x)
-    speeds(S[q], S[n + q], DIM == 2 ? S[2 * n + q] : T(0.0), b[q], g, ax, ay, err);
-  block_speeds(ax, ay, err, out, amask, errp);
 }
 
 // Set a set of ASLOTS speeds to given values (one wavefront).
@@ -821,38 +156,35 @@ __global__ void k_reset(DevScal* s, unsigned long long* sp, double t_end) {
   q[0] = q[1] = 0ull;
 }
 
-// The same and the speeds of the state in one launch, for a grid small enough that at most one workgroup
-// of 1024 per slot reads it quickly: each writes its slot, so nothing need be cleared first. With begin set, it also
-// resets the clock. A launch saved is 4.5 us.
+
+// Threads of a workgroup of k_start.
 constexpr int START_THREADS = 1024;
-template <class T, int DIM>
-__global__ __launch_bounds__(START_THREADS) void k_start(const T* __restrict__ S, const T* __restrict__ b, size_t n, T g,
-                                                         unsigned long long* sp, int set, DevScal* s, int begin,
-                                                         double t_end) {
-  __shared__ double sx[START_THREADS / WAVE], sy[START_THREADS / WAVE];
-  T ax = T(0.0), ay = T(0.0);
-  int err = 0;
-  for (size_t q = (size_t)blockIdx.x * START_THREADS + threadIdx.x; q < n; q += (size_t)gridDim.x * START_THREADS)
-    speeds(S[q], S[n + q], DIM == 2 ? S[2 * n + q] : T(0.0), b[q], g, ax, ay, err);
-  ax = wave_max(ax);
-  ay = wave_max(ay);
-  if (err) atomicOr(&s->err, err);
-  const int w = (int)(threadIdx.x / WAVE), l = (int)(threadIdx.x % WAVE);
-  if (l == 0) { sx[w] = (double)ax; sy[w] = (double)ay; }
-  __syncthreads();
-  if (w != 0) return;
-  const double mx = wave_max(l < START_THREADS / WAVE ? sx[l] : 0.0), my = wave_max(l < START_THREADS / WAVE ? sy[l] : 0.0);
-  unsigned long long* out = sp + (size_t)set * ASET;
-  if (l == 0) {
-    unsigned long long* o = out + (size_t)blockIdx.x * ASTRIDE;
-    o[0] = (unsigned long long)__double_as_longlong(mx);
-    o[1] = (unsigned long long)__double_as_longlong(my);
-  }
-  if (blockIdx.x == 0) {
-    if (l >= (int)gridDim.x) out[(size_t)l * ASTRIDE] = out[(size_t)l * ASTRIDE + 1] = 0ull;
-    if (begin) reset_run(s, sp, t_end, l);
-  }
-}
+// LDS of k_small at R rows per workgroup, in numbers of the arithmetic type.
+constexpr int NNODE = 18;  // slots of a node's fluxes
+constexpr size_t small_lds_words(int R) { return (size_t)WAVE * (R * NNODE + (R + 1) * 14 + R * 6); }
+
+}  // namespace swe
+
+// The scheme's routines and kernels, once per arithmetic type: the two differ in how products and sums become FMAs.
+// Single precision contracts across statements (the compiler's choice per inlined copy); its results near
+// a lake at rest are rounding amplified by 1/dx, so its arithmetic is kept as it is. Double precision contracts within an
+// expression only (0.3% more FP64 instructions), so that every inlined copy of a routine rounds alike and all
+// tilings give the same bits.
+namespace swe32 { using namespace swe; }
+#define SWE_NS swe32
+#include "hweno_device.hpp"
+#include "hweno_stage.inc"
+#undef SWE_NS
+#pragma clang fp contract(on)
+#define SWE_NS swe
+#include "hweno_device.hpp"
+#include "hweno_stage.inc"
+#undef SWE_NS
+#pragma clang fp contract(fast)
+
+#include "hweno_adjoint.hpp"
+
+namespace swe {
 
 __global__ void k_clear_err(DevScal* s) {
   if (threadIdx.x == 0) s->err = 0;
@@ -889,34 +221,6 @@ __global__ void k_setup(DevScal* s, unsigned long long* sp, unsigned long long a
   if (l == 0) {
     s->dt = s->t = s->t_end = s->pad0 = 0.0;
     s->active = s->steps = s->err = s->err0 = 0;
-  }
-}
-
-// Stand-alone limiter: one thread per node, neighbours read directly.
-template <class T, int DIM>
-__global__ __launch_bounds__(256) void k_limit(KArgs<T> a) {
-  const size_t n = (size_t)a.nx * (DIM == 2 ? a.ny : 1);
-  for (size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x; q < n; q += (size_t)gridDim.x * blockDim.x) {
-    const int i = (int)(q % a.nx), j = (int)(q / a.nx);
-    T c0[NREC], xm[NREC], xp[NREC];
-    load_rec<DIM>(a, a.S, i, j, c0);
-    load_rec<DIM>(a, a.S, i - 1, j, xm);
-    load_rec<DIM>(a, a.S, i + 1, j, xp);
-    T D[3];
-    limit_frame(c0[S_ETA], c0[S_M], c0[S_W], c0[S_B], xm[S_ETA], xm[S_M], xm[S_W], xp[S_ETA], xp[S_M], xp[S_W],
-                xm[S_H1], xm[S_M1], xm[S_W1], xp[S_H1], xp[S_M1], xp[S_W1], a.dx, a.idx, a.eps, a.g, D);
-    if (DIM == 1) {
-      a.out[q] = D[0];
-      a.out[n + q] = D[1];
-      continue;
-    }
-    a.out[q] = D[0]; a.out[n + q] = D[1]; a.out[2 * n + q] = D[2];
-    T ym[NREC], yp[NREC];
-    load_rec<DIM>(a, a.S, i, j - 1, ym);
-    load_rec<DIM>(a, a.S, i, j + 1, yp);
-    limit_frame(c0[S_ETA], c0[S_W], c0[S_M], c0[S_B], ym[S_ETA], ym[S_W], ym[S_M], yp[S_ETA], yp[S_W], yp[S_M],
-                ym[S_H2], ym[S_W2], ym[S_M2], yp[S_H2], yp[S_W2], yp[S_M2], a.dy, a.idy, a.eps, a.g, D);
-    a.out[3 * n + q] = D[0]; a.out[4 * n + q] = D[2]; a.out[5 * n + q] = D[1];
   }
 }
 
@@ -990,6 +294,22 @@ unsigned long long dbits(double v) {
   return u;
 }
 
+template <class T> using KArgsOf = std::conditional_t<sizeof(T) == 8, swe::KArgs<T>, swe32::KArgs<T>>;
+// The kernels of an arithmetic type's namespace.
+template <class T> struct Kern;
+template <> struct Kern<double> {
+  template <int DIM, int MODE> static constexpr auto stage = swe::k_stage<double, DIM, MODE>;
+  template <int DIM> static constexpr auto start = swe::k_start<double, DIM>;
+  template <int DIM> static constexpr auto alpha = swe::k_alpha<double, DIM>;
+  template <int DIM> static constexpr auto limit = swe::k_limit<double, DIM>;
+};
+template <> struct Kern<float> {
+  template <int DIM, int MODE> static constexpr auto stage = swe32::k_stage<float, DIM, MODE>;
+  template <int DIM> static constexpr auto start = swe32::k_start<float, DIM>;
+  template <int DIM> static constexpr auto alpha = swe32::k_alpha<float, DIM>;
+  template <int DIM> static constexpr auto limit = swe32::k_limit<float, DIM>;
+};
+
 template <class T> bool is_type(const swe_hweno_ctx* c) { return c->f32 == (sizeof(T) == sizeof(float) ? 1 : 0); }
 
 dim3 stage_grid(const swe_hweno_ctx* c) {
@@ -1008,8 +328,8 @@ int speeds_mask(const swe_hweno_ctx* c) {
   return g.x * g.y <= 48 ? 0 : ASLOTS - 1;
 }
 
-template <class T> KArgs<T> base_args(const swe_hweno_ctx* c) {
-  KArgs<T> a;
+template <class T> KArgsOf<T> base_args(const swe_hweno_ctx* c) {
+  KArgsOf<T> a;
   std::memset(&a, 0, sizeof a);
   a.b = (const T*)c->b; a.bx = (const T*)c->bx; a.by = (const T*)c->by;
   a.sc = c->sc;
@@ -1029,7 +349,7 @@ template <class T> KArgs<T> base_args(const swe_hweno_ctx* c) {
 }
 
 // Speeds read, filled and cleared by the stages of a step (the first stage also forms the step from those of U^n).
-template <class T> void stage_speeds(const swe_hweno_ctx* c, KArgs<T>& a, int stage) {
+template <class A> void stage_speeds(const swe_hweno_ctx* c, A& a, int stage) {
   const bool fa = (c->p.flags & SWE_FIXED_ALPHA) != 0;
   a.a_in = speeds_set(c, fa ? SP_FIX : stage);
   a.a_out = speeds_set(c, (stage + 1) % 3);
@@ -1037,15 +357,15 @@ template <class T> void stage_speeds(const swe_hweno_ctx* c, KArgs<T>& a, int st
   a.a_n = speeds_set(c, SP_N);
 }
 
-template <class T, int MODE> void launch_stage_mode(const swe_hweno_ctx* c, const KArgs<T>& a, hipStream_t s) {
-  if (c->small) {
+template <class T, int MODE> void launch_stage_mode(const swe_hweno_ctx* c, const KArgsOf<T>& a, hipStream_t s) {
+  if constexpr (sizeof(T) == 8) if (c->small) {
     const size_t lds = small_lds_words(c->small) * sizeof(T);
-    if (c->small == 1) hipLaunchKernelGGL((k_small<T, MODE, 4>), stage_grid(c), dim3(4 * WAVE), lds, s, a);
-    else hipLaunchKernelGGL((k_small<T, MODE, 8>), stage_grid(c), dim3(8 * WAVE), lds, s, a);
+    if (c->small == 1) hipLaunchKernelGGL((swe::k_small<T, MODE, 4>), stage_grid(c), dim3(4 * WAVE), lds, s, a);
+    else hipLaunchKernelGGL((swe::k_small<T, MODE, 8>), stage_grid(c), dim3(8 * WAVE), lds, s, a);
     return;
   }
-  if (c->p.dim == 2) hipLaunchKernelGGL((k_stage<T, 2, MODE>), stage_grid(c), dim3(WAVE), 0, s, a);
-  else hipLaunchKernelGGL((k_stage<T, 1, MODE>), stage_grid(c), dim3(WAVE), 0, s, a);
+  if (c->p.dim == 2) hipLaunchKernelGGL((Kern<T>::template stage<2, MODE>), stage_grid(c), dim3(WAVE), 0, s, a);
+  else hipLaunchKernelGGL((Kern<T>::template stage<1, MODE>), stage_grid(c), dim3(WAVE), 0, s, a);
 }
 
 // Speeds of a state into a set; with begin (set SP_N), at the start of a run or step whose clock it resets.
@@ -1058,10 +378,10 @@ template <class T> void launch_alpha(const swe_hweno_ctx* c, const T* S, int set
   if (c->n <= most) {
     const size_t blocks = amask ? std::min<size_t>((c->n + START_THREADS - 1) / START_THREADS, ASLOTS) : 1;
     if (c->p.dim == 2)
-      hipLaunchKernelGGL((k_start<T, 2>), dim3((unsigned)blocks), dim3(START_THREADS), 0, s, S, b, c->n, T(c->p.g), c->sp,
+      hipLaunchKernelGGL((Kern<T>::template start<2>), dim3((unsigned)blocks), dim3(START_THREADS), 0, s, S, b, c->n, T(c->p.g), c->sp,
                          set, c->sc, begin ? 1 : 0, t_end);
     else
-      hipLaunchKernelGGL((k_start<T, 1>), dim3((unsigned)blocks), dim3(START_THREADS), 0, s, S, b, c->n, T(c->p.g), c->sp,
+      hipLaunchKernelGGL((Kern<T>::template start<1>), dim3((unsigned)blocks), dim3(START_THREADS), 0, s, S, b, c->n, T(c->p.g), c->sp,
                          set, c->sc, begin ? 1 : 0, t_end);
     return;
   }
@@ -1072,9 +392,9 @@ template <class T> void launch_alpha(const swe_hweno_ctx* c, const T* S, int set
   const size_t blocks = (c->n + 255) / 256;
   const unsigned grid = (unsigned)(blocks < 2048 ? blocks : 2048);
   if (c->p.dim == 2)
-    hipLaunchKernelGGL((k_alpha<T, 2>), dim3(grid), dim3(256), 0, s, S, b, c->n, T(c->p.g), out, amask, &c->sc->err);
+    hipLaunchKernelGGL((Kern<T>::template alpha<2>), dim3(grid), dim3(256), 0, s, S, b, c->n, T(c->p.g), out, amask, &c->sc->err);
   else
-    hipLaunchKernelGGL((k_alpha<T, 1>), dim3(grid), dim3(256), 0, s, S, b, c->n, T(c->p.g), out, amask, &c->sc->err);
+    hipLaunchKernelGGL((Kern<T>::template alpha<1>), dim3(grid), dim3(256), 0, s, S, b, c->n, T(c->p.g), out, amask, &c->sc->err);
 }
 
 hipEvent_t take_event(swe_hweno_ctx* c) {
@@ -1120,12 +440,12 @@ void collect_timing(swe_hweno_ctx* c) {
 // One step on stream s: three fused stages; U^n is `state`, updated in place.
 // With timing on (direct launches only) every stage kernel is bracketed by an event pair.
 template <class T> void enqueue_step(swe_hweno_ctx* c, T* state, int use_tend, hipStream_t s) {
-  KArgs<T> base = base_args<T>(c);
+  KArgsOf<T> base = base_args<T>(c);
   base.use_tend = use_tend;
   T* S1 = (T*)c->S1;
   T* S2 = (T*)c->S2;
   T* Dn = (T*)c->Dn;
-  KArgs<T> a = base;
+  KArgsOf<T> a = base;
   stage_speeds(c, a, 0);
   a.S = state; a.out = S1; a.Dn_out = Dn;
   int id = time_begin(c, s);
@@ -1173,8 +493,9 @@ int choose_rows(int nx, int ny, int slots) {
 // Rows per workgroup of k_small, or 0 for marching wavefronts: the fewest for which every workgroup is resident at
 // once, one per CU, up to 8 (their LDS). With one row a workgroup has 4 wavefronts, one per SIMD, else 8. A further
 // row costs about 1.5 us, from 7.7 us at one row to 17.8 at 8; marching wavefronts take 19.3 us at their shortest marches, 22
-// where this rule ends (about 340^2), and 24 at 400^2, where two rounds of 6 rows take 28.7. In single
-// precision 6.9 to 13.3 us against 16.9. A choice of rows by the environment keeps the marching wavefronts.
+// where this rule ends (about 340^2), and 24 at 400^2, where two rounds of 6 rows take 28.7. Double
+// precision only: in single precision (6.9 to 13.3 us against 16.9) the two tilings would round differently. A choice of
+// rows by the environment keeps the marching wavefronts.
 constexpr int SMALL_ROWS = 8;
 int choose_small(int nx, int ny, int cus) {
   if (std::getenv("SWE_HWENO_ROWS")) return 0;
@@ -1191,7 +512,7 @@ void choose_tile(swe_hweno_ctx* c) {
       hipSuccess || cus <= 0)
     cus = 256;
   c->rows = choose_rows(c->p.nx, c->p.dim == 2 ? c->p.ny : 1, 4 * cus);
-  c->small = c->p.dim == 2 ? choose_small(c->p.nx, c->p.ny, cus) : 0;
+  c->small = c->p.dim == 2 && !c->f32 ? choose_small(c->p.nx, c->p.ny, cus) : 0;
 }
 
 int take_device_error(swe_hweno_ctx* c) {
@@ -1282,7 +603,7 @@ template <class T> int rhs_impl(swe_hweno_ctx* c, const T* state, T* rhs, double
   else
     hipLaunchKernelGGL(k_set_speeds, dim3(1), dim3(ASLOTS), 0, c->stream, speeds_set(c, SP_RHS), dbits(alpha_x),
                        dbits(c->p.dim == 2 ? alpha_y : 0.0));
-  KArgs<T> a = base_args<T>(c);
+  KArgsOf<T> a = base_args<T>(c);
   a.S = state; a.out = rhs; a.a_in = speeds_set(c, SP_RHS);
   const int id = time_begin(c, c->stream);
   launch_stage_mode<T, MODE_RHS>(c, a, c->stream);
@@ -1293,12 +614,12 @@ template <class T> int rhs_impl(swe_hweno_ctx* c, const T* state, T* rhs, double
 
 template <class T> int limit_impl(swe_hweno_ctx* c, const T* state, T* dmod) {
   if (!c || !state || !dmod || !is_type<T>(c)) return SWE_EINVAL;
-  KArgs<T> a = base_args<T>(c);
+  KArgsOf<T> a = base_args<T>(c);
   a.S = state; a.out = dmod;
   const size_t blocks = (c->n + 255) / 256;
   const unsigned grid = (unsigned)(blocks < 8192 ? blocks : 8192);
-  if (c->p.dim == 2) hipLaunchKernelGGL((k_limit<T, 2>), dim3(grid), dim3(256), 0, c->stream, a);
-  else hipLaunchKernelGGL((k_limit<T, 1>), dim3(grid), dim3(256), 0, c->stream, a);
+  if (c->p.dim == 2) hipLaunchKernelGGL((Kern<T>::template limit<2>), dim3(grid), dim3(256), 0, c->stream, a);
+  else hipLaunchKernelGGL((Kern<T>::template limit<1>), dim3(grid), dim3(256), 0, c->stream, a);
   return hip_status(hipGetLastError());
 }
 

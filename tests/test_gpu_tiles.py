@@ -26,15 +26,14 @@ def _solver(pr, rows, dtype, **kw):
             os.environ["SWE_HWENO_ROWS"] = old
 
 
-@pytest.mark.parametrize("single", [False, True])
 @pytest.mark.parametrize("nx,ny,rows", SHAPES)
-def test_small_tiles_give_the_bits_of_marches(nx, ny, rows, single):
+def test_small_tiles_give_the_bits_of_marches(nx, ny, rows):
     import torch
 
     from paper_2208_01260_amd import inputs
     from paper_2208_01260_amd._lib import NO_LIMITER
 
-    dtype = torch.float32 if single else torch.float64
+    dtype = torch.float64
     pr = inputs.c3_2d(nx, ny=ny)  # walls, a dam break
     if (nx + ny) % 2:
         pr.bc = (0, 0)  # periodic
