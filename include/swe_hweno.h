@@ -90,6 +90,15 @@ typedef struct {
 int swe_hweno_init(const swe_hweno_params* params, const double* b, const double* bx, const double* by,
                    void* stream, swe_hweno_ctx** out);
 
+/* The same context in device memory of the caller's (a program with a memory pool of its own, which makes
+ * and drops contexts without device allocations): mem, on a boundary of 256 bytes, has at least
+ * swe_hweno_context_bytes(params, single) bytes, is the context's alone until swe_hweno_destroy has
+ * returned and is not freed by the library. single selects float (as swe_hweno_init_f32), with b, bx and
+ * by of that type. swe_hweno_context_bytes is host-only and returns 0 for invalid params. */
+unsigned long swe_hweno_context_bytes(const swe_hweno_params* params, int single);
+int swe_hweno_init_in(const swe_hweno_params* params, int single, const void* b, const void* bx, const void* by,
+                      void* stream, void* mem, unsigned long bytes, swe_hweno_ctx** out);
+
 /* Right-hand side R(state) of the semi-discrete scheme (eq. (2.8) / (3.8)): rhs has the layout
  * of state. alpha_x < 0 computes alpha from the state on the device (then alpha_y is ignored);
  * otherwise the given alpha_x (and alpha_y in 2D) are used and must be finite and positive
@@ -111,7 +120,7 @@ int swe_hweno_alpha(swe_hweno_ctx* ctx, const double* state, double* alpha_host)
 int swe_hweno_step(swe_hweno_ctx* ctx, double* state, double dt, double* dt_used);
 
 /* nsteps SSP-RK3 steps (eq. (2.11) of Sec. 2.2, each as swe_hweno_step) of state in place,
- * replaying a captured per-step HIP graph. With t_end > 0 it stops at t_end (the last step
+ * replaying a captured per-step HIP graph after the first 256 steps on one state array. With t_end > 0 it stops at t_end (the last step
  * clipped to it; nsteps <= 0 means "until t_end"); t_out and steps_out (HOST, nullable) receive
  * the time reached and the steps taken. Synchronises and returns device-detected errors. */
 int swe_hweno_run(swe_hweno_ctx* ctx, double* state, int nsteps, double t_end, double* t_out, int* steps_out);
@@ -267,8 +276,8 @@ void swe_hweno_batch_destroy(swe_hweno_batch* bt);
  * The bottom b and its slopes bx, by enter as independent inputs; swe_hweno_bottom_slopes and
  * its transpose tie them together when the gradient with respect to b alone is wanted. Work
  * buffers are allocated on first use and kept with the context until swe_hweno_destroy: about
- * 170 planes of nx*ny doubles, plus 27 per step of the checkpoint interval (the recomputed stage
- * states of one segment) and 9 per checkpoint. All arrays are DEVICE arrays; outputs are
+ * 85 planes of nx*ny doubles, plus 27 per step of the checkpoint interval (the recomputed stage
+ * states of one segment) and 9 per checkpoint (or they are the caller's, swe_hweno_adjoint_memory). All arrays are DEVICE arrays; outputs are
  * overwritten. FP64 contexts only (an FP32 context returns SWE_EINVAL).
  * ------------------------------------------------------------------------------------------ */
 
@@ -301,6 +310,15 @@ int swe_hweno_run_vjp(swe_hweno_ctx* ctx, const double* state0, int nsteps, int 
 int swe_hweno_run_checkpointed(swe_hweno_ctx* ctx, double* state, int nsteps, int checkpoint_every);
 int swe_hweno_run_vjp_checkpointed(swe_hweno_ctx* ctx, int nsteps, int checkpoint_every, const double* sbar_T,
                                    double* sbar_0, double* bbar, double* bxbar, double* bybar);
+
+/* Work memory of the adjoint from the caller, instead of allocations on first use: mem, on a boundary of
+ * 256 bytes, is the context's alone until it is replaced by another call (which synchronises the
+ * stream first and discards saved checkpoints) or swe_hweno_destroy has returned, and is not freed by
+ * the library. swe_hweno_adjoint_bytes is what a run of nsteps steps with that checkpoint interval needs (nsteps
+ * = 0: the right-hand side's and the limiter's products); 0 for a context or arguments that have no
+ * adjoint. A later call that needs more returns SWE_ENOMEM. */
+unsigned long swe_hweno_adjoint_bytes(const swe_hweno_ctx* ctx, int nsteps, int checkpoint_every);
+int swe_hweno_adjoint_memory(swe_hweno_ctx* ctx, void* mem, unsigned long bytes);
 
 /* Bottom slopes by the fourth-order centred difference
  *   bx_i = (b_{i-2} - 8 b_{i-1} + 8 b_{i+1} - b_{i+2}) / (12 dx)   (by likewise along y),

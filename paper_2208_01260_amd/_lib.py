@@ -29,7 +29,8 @@ EXPORTS = ("swe_hweno_init", "swe_hweno_rhs", "swe_hweno_limit", "swe_hweno_alph
            "swe_hweno_rhs_vjp", "swe_hweno_limit_vjp", "swe_hweno_run_vjp", "swe_hweno_bottom_slopes",
            "swe_hweno_bottom_slopes_vjp", "swe_hweno_run_checkpointed", "swe_hweno_run_vjp_checkpointed",
            "swe_hweno_step_noalloc", "swe_hweno_noalloc_capacity", "swe_hweno_math_check",
-           "swe_hweno_source_hash")
+           "swe_hweno_source_hash", "swe_hweno_context_bytes", "swe_hweno_init_in", "swe_hweno_adjoint_bytes",
+           "swe_hweno_adjoint_memory")
 
 
 class SweError(RuntimeError):
@@ -109,6 +110,10 @@ def lib() -> ctypes.CDLL:
         "swe_hweno_noalloc_capacity": (ctypes.c_ulong, []),
         "swe_hweno_math_check": (I, [I, dp, dp, ctypes.c_ulong, vp]),
         "swe_hweno_source_hash": (ctypes.c_char_p, []),
+        "swe_hweno_context_bytes": (ctypes.c_ulong, [P, I]),
+        "swe_hweno_init_in": (I, [P, I, dp, dp, dp, vp, vp, ctypes.c_ulong, ctypes.POINTER(vp)]),
+        "swe_hweno_adjoint_bytes": (ctypes.c_ulong, [vp, I, I]),
+        "swe_hweno_adjoint_memory": (I, [vp, vp, ctypes.c_ulong]),
     }
     for name, (res, args) in sig.items():
         fn = getattr(L, name)

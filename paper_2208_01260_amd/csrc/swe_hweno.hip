@@ -237,7 +237,8 @@ struct swe_hweno_ctx {
   hipStream_t cap = nullptr;  // capture stream for the per-step graphs
   int nf = 0, nd = 0;
   size_t n = 0;
-  void* mem = nullptr;        // the one device allocation that the pointers below point into
+  void* mem = nullptr;        // the one block of device memory that the pointers below point into
+  bool own_mem = false;       // allocated here (else the caller's)
   void *b = nullptr, *bx = nullptr, *by = nullptr;  // planes of the context's type
   void *S1 = nullptr, *S2 = nullptr, *Dn = nullptr;
   DevScal* sc = nullptr;
@@ -245,6 +246,7 @@ struct swe_hweno_ctx {
   hipGraphExec_t g1 = nullptr, g8 = nullptr;
   const void* g_state = nullptr;
   int g_tend = 0;
+  long g_steps = 0;  // steps launched on g_state before its graphs were captured
   int rows = ROWS_DEFAULT;  // rows marched per wave (2D), chosen at init
   int small = 0;            // 2D: rows per workgroup of k_small, or 0 for marching wavefronts
   // kernel timing: event pairs around stage kernels (slot 0 = bare right-hand side, 1..3 = stages)
@@ -515,14 +517,17 @@ void choose_tile(swe_hweno_ctx* c) {
   c->small = c->p.dim == 2 && !c->f32 ? choose_small(c->p.nx, c->p.ny, cus) : 0;
 }
 
-int take_device_error(swe_hweno_ctx* c) {
-  int e = 0;
-  if (hipMemcpyAsync(&e, &c->sc->err, sizeof(int), hipMemcpyDeviceToHost, c->stream) != hipSuccess) return SWE_EHIP;
+// The device scalars in one copy (every copy to pageable memory costs a round trip), and the error they report,
+// which is cleared.
+int take_device_error(swe_hweno_ctx* c, DevScal* out = nullptr) {
+  DevScal s;
+  if (hipMemcpyAsync(&s, c->sc, sizeof s, hipMemcpyDeviceToHost, c->stream) != hipSuccess) return SWE_EHIP;
   if (hipStreamSynchronize(c->stream) != hipSuccess) return SWE_EHIP;
-  if (e) {
+  if (out) *out = s;
+  if (s.err) {
     hipLaunchKernelGGL(k_clear_err, dim3(1), dim3(64), 0, c->stream, c->sc);
     if (hipStreamSynchronize(c->stream) != hipSuccess) return SWE_EHIP;
-    return (e & ERR_NONFINITE) ? SWE_ENONFINITE : SWE_EDRY;
+    return (s.err & ERR_NONFINITE) ? SWE_ENONFINITE : SWE_EDRY;
   }
   return SWE_OK;
 }
@@ -545,13 +550,32 @@ template <class T> int capture(swe_hweno_ctx* c, T* state, int steps, int use_te
 }
 
 // ------------------------------------------------------------------ typed bodies of the entry points
+// Places in a context's block: the scalars, the sets of speeds and the planes, each on a boundary of 256 bytes.
+struct CtxLayout { size_t sp, b, s1, s2, dn, bytes; };
+CtxLayout ctx_layout(const swe_hweno_params* p, size_t esz) {
+  const auto up = [](size_t v) { return (v + 255) / 256 * 256; };
+  const size_t plane = (size_t)p->nx * (size_t)(p->dim == 2 ? p->ny : 1) * esz, nf = p->dim == 2 ? 9 : 4;
+  CtxLayout l;
+  l.sp = up(sizeof(DevScal));
+  l.b = up(l.sp + sizeof(unsigned long long) * SP_SETS * ASET);
+  l.s1 = up(l.b + 3 * plane);
+  l.s2 = up(l.s1 + nf * plane);
+  l.dn = up(l.s2 + nf * plane);
+  l.bytes = up(l.dn + (p->dim == 2 ? 6 : 2) * plane);
+  return l;
+}
+
+// A context in `mem` (bytes of it), or in memory allocated here if mem is null.
 template <class T>
-int init_impl(const swe_hweno_params* p, const T* b, const T* bx, const T* by, void* stream, swe_hweno_ctx** out) {
+int init_impl(const swe_hweno_params* p, const T* b, const T* bx, const T* by, void* stream, void* mem, size_t bytes,
+              swe_hweno_ctx** out) {
   if (!out) return SWE_EINVAL;
   *out = nullptr;
   if (!params_ok(p) || !b || !bx || (p->dim == 2 && !by)) return SWE_EINVAL;
   // single precision: the weights, of order eps^4 where the data are flat, stay normal floats
   if (sizeof(T) == 4 && !(p->eps >= 1e-9)) return SWE_EINVAL;
+  const CtxLayout at = ctx_layout(p, sizeof(T));
+  if (mem && (bytes < at.bytes || (uintptr_t)mem % 256)) return SWE_EINVAL;
   swe_hweno_ctx* c = new (std::nothrow) swe_hweno_ctx();
   if (!c) return SWE_ENOMEM;
   c->p = *p;
@@ -562,18 +586,20 @@ int init_impl(const swe_hweno_params* p, const T* b, const T* bx, const T* by, v
   c->nd = p->dim == 2 ? 6 : 2;
   c->n = (size_t)p->nx * (size_t)(p->dim == 2 ? p->ny : 1);
   const size_t plane = c->n * sizeof(T);
-  // one allocation: the scalars, the sets of speeds and the planes, each on a boundary of 256 bytes
-  const auto up = [](size_t v) { return (v + 255) / 256 * 256; };
-  const size_t at_sp = up(sizeof(DevScal)), at_b = up(at_sp + sizeof(unsigned long long) * SP_SETS * ASET);
-  const size_t at_s1 = up(at_b + 3 * plane), at_s2 = up(at_s1 + c->nf * plane), at_dn = up(at_s2 + c->nf * plane);
-  if (hipMalloc(&c->mem, at_dn + c->nd * plane) != hipSuccess) { swe_hweno_destroy(c); return SWE_ENOMEM; }
+  c->mem = mem;
+  c->own_mem = mem == nullptr;
+  if (!mem && hipMalloc(&c->mem, at.bytes) != hipSuccess) {
+    c->mem = nullptr;
+    swe_hweno_destroy(c);
+    return SWE_ENOMEM;
+  }
   char* base = (char*)c->mem;
   c->sc = (DevScal*)base;
-  c->sp = (unsigned long long*)(base + at_sp);
-  c->b = base + at_b;
-  c->S1 = base + at_s1;
-  c->S2 = base + at_s2;
-  c->Dn = base + at_dn;
+  c->sp = (unsigned long long*)(base + at.sp);
+  c->b = base + at.b;
+  c->S1 = base + at.s1;
+  c->S2 = base + at.s2;
+  c->Dn = base + at.dn;
   c->bx = (T*)c->b + c->n;
   c->by = (T*)c->b + 2 * c->n;
   choose_tile(c);
@@ -648,24 +674,25 @@ template <class T> int step_impl(swe_hweno_ctx* c, T* state, double dt, double* 
   c->p = saved;
   if (hipGetLastError() != hipSuccess) return SWE_EHIP;
   if (dt_used) {
-    if (hipMemcpyAsync(dt_used, &c->sc->dt, sizeof(double), hipMemcpyDeviceToHost, c->stream) != hipSuccess)
-      return SWE_EHIP;
-    return take_device_error(c);
+    DevScal s;
+    const int e = take_device_error(c, &s);
+    if (e != SWE_EHIP) *dt_used = s.dt;
+    return e;
   }
   return (c->p.flags & SWE_CHECK_DRY) ? take_device_error(c) : SWE_OK;
 }
+
+constexpr long GRAPH_AFTER = 256;
 
 template <class T> int run_impl(swe_hweno_ctx* c, T* state, int nsteps, double t_end, double* t_out, int* steps_out) {
   if (!c || !state || !is_type<T>(c)) return SWE_EINVAL;
   if (!(t_end <= DBL_MAX) || (nsteps <= 0 && !(t_end > 0))) return SWE_EINVAL;
   const int use_tend = t_end > 0 ? 1 : 0;
-  if (!c->timing && (c->g_state != state || c->g_tend != use_tend)) {
+  if (c->g_state != state || c->g_tend != use_tend) {
     destroy_graphs(c);
-    int e = capture<T>(c, state, 1, use_tend, &c->g1);
-    if (!e) e = capture<T>(c, state, 8, use_tend, &c->g8);
-    if (e) { destroy_graphs(c); return e; }
     c->g_state = state;
     c->g_tend = use_tend;
+    c->g_steps = 0;
   }
   // t = 0, t_end, steps = 0 and alpha of the initial state
   launch_alpha<T>(c, state, SP_N, true, t_end, c->stream);
@@ -677,9 +704,19 @@ template <class T> int run_impl(swe_hweno_ctx* c, T* state, int nsteps, double t
     if (todo <= 0) break;
     if (use_tend && todo > chunk) todo = chunk;
     int k = 0;
-    if (c->timing) {
-      for (; k < todo; ++k) enqueue_step<T>(c, state, use_tend, c->stream);
+    // capturing costs what the replays of some 200 steps save (120 us; a replayed step of small kernels is
+    // 2 to 4% faster than its three launches), so the first steps on a state are launched directly
+    if (c->timing || (!c->g8 && c->g_steps < GRAPH_AFTER)) {
+      for (; k < todo && (c->timing || c->g_steps < GRAPH_AFTER); ++k) {
+        enqueue_step<T>(c, state, use_tend, c->stream);
+        if (!c->timing) c->g_steps += 1;
+      }
       if (hipGetLastError() != hipSuccess) return SWE_EHIP;
+    }
+    if (k < todo && !c->g8) {
+      int e = capture<T>(c, state, 1, use_tend, &c->g1);
+      if (!e) e = capture<T>(c, state, 8, use_tend, &c->g8);
+      if (e) { destroy_graphs(c); return e; }
     }
     for (; k + 8 <= todo; k += 8)
       if (hipGraphLaunch(c->g8, c->stream) != hipSuccess) return SWE_EHIP;
@@ -694,15 +731,12 @@ template <class T> int run_impl(swe_hweno_ctx* c, T* state, int nsteps, double t
       if (!active) break;
     }
   }
-  double t = 0;
-  int steps = 0;
-  if (hipMemcpyAsync(&t, &c->sc->t, sizeof t, hipMemcpyDeviceToHost, c->stream) != hipSuccess) return SWE_EHIP;
-  if (hipMemcpyAsync(&steps, &c->sc->steps, sizeof steps, hipMemcpyDeviceToHost, c->stream) != hipSuccess)
-    return SWE_EHIP;
-  const int e = take_device_error(c);
+  DevScal s;
+  const int e = take_device_error(c, &s);
+  if (e == SWE_EHIP) return e;
   if (c->timing) collect_timing(c);
-  if (t_out) *t_out = t;
-  if (steps_out) *steps_out = steps;
+  if (t_out) *t_out = s.t;
+  if (steps_out) *steps_out = s.steps;
   return e;
 }
 
@@ -765,9 +799,10 @@ int step_noalloc_impl(const swe_hweno_params* p, double* state, const double* b,
   enqueue_step<double>(&c, state, 0, c.stream);
   if (hipGetLastError() != hipSuccess) return SWE_EHIP;
   if (dt_used) {
-    if (hipMemcpyAsync(dt_used, &c.sc->dt, sizeof(double), hipMemcpyDeviceToHost, c.stream) != hipSuccess)
-      return SWE_EHIP;
-    return take_device_error(&c);
+    DevScal s;
+    const int e = take_device_error(&c, &s);
+    if (e != SWE_EHIP) *dt_used = s.dt;
+    return e;
   }
   return SWE_OK;
 }
@@ -806,11 +841,21 @@ const char* swe_hweno_strerror(int code) {
 
 int swe_hweno_init(const swe_hweno_params* p, const double* b, const double* bx, const double* by, void* stream,
                    swe_hweno_ctx** out) {
-  return init_impl<double>(p, b, bx, by, stream, out);
+  return init_impl<double>(p, b, bx, by, stream, nullptr, 0, out);
 }
 int swe_hweno_init_f32(const swe_hweno_params* p, const float* b, const float* bx, const float* by, void* stream,
                        swe_hweno_ctx** out) {
-  return init_impl<float>(p, b, bx, by, stream, out);
+  return init_impl<float>(p, b, bx, by, stream, nullptr, 0, out);
+}
+unsigned long swe_hweno_context_bytes(const swe_hweno_params* p, int single) {
+  return params_ok(p) ? (unsigned long)ctx_layout(p, single ? sizeof(float) : sizeof(double)).bytes : 0;
+}
+int swe_hweno_init_in(const swe_hweno_params* p, int single, const void* b, const void* bx, const void* by, void* stream,
+                      void* mem, unsigned long bytes, swe_hweno_ctx** out) {
+  if (out) *out = nullptr;
+  if (!mem) return SWE_EINVAL;
+  if (single) return init_impl<float>(p, (const float*)b, (const float*)bx, (const float*)by, stream, mem, bytes, out);
+  return init_impl<double>(p, (const double*)b, (const double*)bx, (const double*)by, stream, mem, bytes, out);
 }
 
 void swe_hweno_destroy(swe_hweno_ctx* c) {
@@ -820,7 +865,7 @@ void swe_hweno_destroy(swe_hweno_ctx* c) {
   collect_timing(c);
   for (hipEvent_t e : c->pool) (void)hipEventDestroy(e);
   if (c->cap) (void)hipStreamDestroy(c->cap);
-  if (c->mem) (void)hipFree(c->mem);
+  if (c->mem && c->own_mem) (void)hipFree(c->mem);
   swe_adj_release(c);
   delete c;
 }

@@ -37,6 +37,7 @@ class Solver:
         self.dtype = dtype
         sfx = "_f32" if dtype == torch.float32 else ""
         self._fn = {k: getattr(L, f"swe_hweno_{k}{sfx}") for k in ("init", "rhs", "limit", "alpha", "step", "run")}
+        self._adj = None
         self.dim, self.nx, self.ny = dim, nx, (ny if dim == 2 else 1)
         self.nf = 9 if dim == 2 else 4
         self.shape = (9, self.ny, nx) if dim == 2 else (4, nx)
@@ -54,10 +55,28 @@ class Solver:
             if t.numel() != nx * self.ny:
                 raise ValueError("bottom planes must have nx*ny elements")
         ctx = ctypes.c_void_p()
-        _lib.check(self._fn["init"](ctypes.byref(p), ptrs[0], ptrs[1], ptrs[2] if dim == 2 else None,
-                                    ctypes.c_void_p(self.stream.cuda_stream), ctypes.byref(ctx)), "swe_hweno_init")
+        planes = (ptrs[0], ptrs[1], ptrs[2] if dim == 2 else None)
+        self._mem = self._block(L.swe_hweno_context_bytes(ctypes.byref(p), 1 if sfx else 0))
+        if self._mem is not None:
+            rc = L.swe_hweno_init_in(ctypes.byref(p), 1 if sfx else 0, *planes, ctypes.c_void_p(self.stream.cuda_stream),
+                                     self._mem.data_ptr(), self._mem.numel(), ctypes.byref(ctx))
+        else:
+            rc = self._fn["init"](ctypes.byref(p), *planes, ctypes.c_void_p(self.stream.cuda_stream), ctypes.byref(ctx))
+        _lib.check(rc, "swe_hweno_init")
         self._ctx = ctx
         self._L = L
+
+    def _block(self, nbytes):
+        """Device memory for the library from torch's allocator, which keeps and reuses it (allocating a gradient's
+        buffers anew took 1 to 5 ms of each call, and at times 100), on the solver's stream; None if there
+        is not enough (the library then allocates, or reports it)."""
+        if nbytes == 0 or not isinstance(self.stream, torch.cuda.Stream):
+            return None
+        try:
+            with torch.cuda.stream(self.stream):
+                return torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        except torch.cuda.OutOfMemoryError:
+            return None
 
     @classmethod
     def from_problem(cls, prob, device="cuda", dtype=torch.float64, **kw):
@@ -128,8 +147,18 @@ class Solver:
     def _planes(self, like=None):
         return torch.empty((self.ny, self.nx), dtype=torch.float64, device="cuda") if like is None else like
 
+    def _adjoint_memory(self, nsteps=0, checkpoint_every=1):
+        """Work memory of the adjoint for a run (or a single product), before the call that needs it."""
+        need = self._L.swe_hweno_adjoint_bytes(self._ctx, int(nsteps), int(checkpoint_every))
+        if need and (self._adj is None or self._adj.numel() < need):
+            mem = self._block(need)
+            if mem is not None:
+                _lib.check(self._L.swe_hweno_adjoint_memory(self._ctx, mem.data_ptr(), need), "swe_hweno_adjoint_memory")
+                self._adj = mem
+
     def rhs_vjp(self, state, rbar, alpha):
         """(sbar, bbar, bxbar, bybar) = rbar^T d R(state) / d(state, b, bx, by), alpha frozen."""
+        self._adjoint_memory()
         sbar = torch.empty_like(state)
         bb, bxb, byb = self._planes(), self._planes(), self._planes()
         _lib.check(self._L.swe_hweno_rhs_vjp(self._ctx, self._state(state), float(alpha[0]), float(alpha[1]),
@@ -139,6 +168,7 @@ class Solver:
 
     def limit_vjp(self, state, dmbar):
         """(sbar, bbar) = dmbar^T d Lim(state) / d(state, b)."""
+        self._adjoint_memory()
         sbar = torch.empty_like(state)
         bb = self._planes()
         dshape = (6, self.ny, self.nx)
@@ -150,6 +180,7 @@ class Solver:
     def run_checkpointed(self, state, nsteps, checkpoint_every=10):
         """nsteps fixed-dt, frozen-alpha steps of state in place, keeping checkpoints for
         run_vjp_checkpointed."""
+        self._adjoint_memory(nsteps, checkpoint_every)
         _lib.check(self._L.swe_hweno_run_checkpointed(self._ctx, self._state(state), int(nsteps),
                                                       int(checkpoint_every)), "swe_hweno_run_checkpointed")
 
@@ -166,6 +197,7 @@ class Solver:
     def run_vjp(self, state0, nsteps, sbar_T, checkpoint_every=10):
         """Reverse of `nsteps` fixed-dt, frozen-alpha steps from state0: returns
         (sbar_0, bbar, bxbar, bybar) for the adjoint sbar_T of the final state."""
+        self._adjoint_memory(nsteps, checkpoint_every)
         sbar0 = torch.empty_like(state0)
         bb, bxb, byb = self._planes(), self._planes(), self._planes()
         _lib.check(self._L.swe_hweno_run_vjp(self._ctx, self._state(state0), int(nsteps), int(checkpoint_every),
@@ -175,8 +207,8 @@ class Solver:
 
     def close(self):
         if getattr(self, "_ctx", None) is not None and self._ctx.value:
-            self._L.swe_hweno_destroy(self._ctx)
-            self._ctx = None
+            self._L.swe_hweno_destroy(self._ctx)  # synchronises the stream, so the memory may be reused
+            self._ctx = self._mem = self._adj = None
 
     def __del__(self):
         try:
