@@ -350,4 +350,23 @@ __device__ __forceinline__ void limit_frame(T e0, T mn0, T mt0, T b0, T em, T mn
   out[2] = ut * (v1 + v3) + v2;
 }
 
+// limit_frame in one dimension (double precision): no tangential component, and the two others share one
+// reciprocal of the product of their weight sums.
+template <class T>
+__device__ __forceinline__ void limit_line(T e0, T mn0, T b0, T em, T mnm, T ep, T mnp, T dm0, T dm1, T dp0, T dp1, T dx,
+                                           T idx, T eps, T g, T out[2]) {
+  const T h = e0 - b0, ih = rcp(h);
+  const T un = mn0 * ih;
+  const T cs = sqrt_pos(g * h), i2c = T(0.5) * rcp(cs);
+  const T l1a = (un + cs) * i2c, l3a = (cs - un) * i2c;
+  const LimNS<T> c1 = limit_char_ns(l1a * em - i2c * mnm, l1a * e0 - i2c * mn0, l1a * ep - i2c * mnp,
+                                    l1a * dm0 - i2c * dm1, l1a * dp0 - i2c * dp1, dx, eps);
+  const LimNS<T> c3 = limit_char_ns(l3a * em + i2c * mnm, l3a * e0 + i2c * mn0, l3a * ep + i2c * mnp,
+                                    l3a * dm0 + i2c * dm1, l3a * dp0 + i2c * dp1, dx, eps);
+  const T r = rcp(c1.s * c3.s) * idx;
+  const T v1 = (c1.n * c3.s) * r, v3 = (c3.n * c1.s) * r;
+  out[0] = v1 + v3;
+  out[1] = (un - cs) * v1 + (un + cs) * v3;
+}
+
 }  // namespace SWE_NS

@@ -273,6 +273,7 @@ struct swe_hweno_ctx {
   long g_steps = 0;  // steps launched on g_state before its graphs were captured
   int rows = ROWS_DEFAULT;  // rows marched per wave (2D), chosen at init
   int small = 0;            // 2D: rows per workgroup of k_small, or 0 for marching wavefronts
+  int line = 0;             // 1D: wavefronts of k_line's workgroup, or 0 for a launch per stage
   // kernel timing: event pairs around stage kernels (slot 0 = bare right-hand side, 1..3 = stages)
   bool timing = false;
   struct Pending { hipEvent_t a, b; int slot; };
@@ -463,6 +464,27 @@ void collect_timing(swe_hweno_ctx* c) {
   c->pending.clear();
 }
 
+// nsteps steps of a 1D grid in one launch (rhs null), or its right-hand side with given speeds (alpha > 0) or the state's.
+void launch_line(const swe_hweno_ctx* c, double* state, double* rhs, int nsteps, bool begin, int use_tend, double t_end,
+                 double alpha, hipStream_t s) {
+  swe::LineArgs<double> a;
+  std::memset(&a, 0, sizeof a);
+  a.state = state; a.rhs = rhs;
+  a.b = (const double*)c->b; a.bx = (const double*)c->bx;
+  a.sc = c->sc;
+  a.nx = c->p.nx; a.bc = c->p.bc_x;
+  a.limiter = (c->p.flags & SWE_NO_LIMITER) ? 0 : 1;
+  a.nsteps = nsteps; a.begin = begin ? 1 : 0; a.use_tend = use_tend;
+  a.fixed_dt = (c->p.flags & SWE_FIXED_DT) ? 1 : 0;
+  a.fixed_alpha = rhs ? alpha > 0 : (c->p.flags & SWE_FIXED_ALPHA) != 0;
+  a.alpha = rhs ? alpha : c->p.alpha_x;
+  a.t_end = t_end; a.cfl = c->p.cfl; a.fdt = c->p.fixed_dt;
+  a.cdx = (c->p.x1 - c->p.x0) / c->p.nx;
+  a.dx = a.cdx; a.idx = 1.0 / a.cdx; a.g = c->p.g; a.eps = c->p.eps;
+  if (rhs) hipLaunchKernelGGL((swe::k_line<double, true>), dim3(1), dim3(c->line * WAVE), 0, s, a);
+  else hipLaunchKernelGGL((swe::k_line<double, false>), dim3(1), dim3(c->line * WAVE), 0, s, a);
+}
+
 // One step on stream s: three fused stages; U^n is `state`, updated in place.
 // With timing on (direct launches only) every stage kernel is bracketed by an event pair.
 template <class T> void enqueue_step(swe_hweno_ctx* c, T* state, int use_tend, hipStream_t s) {
@@ -539,6 +561,9 @@ void choose_tile(swe_hweno_ctx* c) {
     cus = 256;
   c->rows = choose_rows(c->p.nx, c->p.dim == 2 ? c->p.ny : 1, 4 * cus);
   c->small = c->p.dim == 2 && !c->f32 ? choose_small(c->p.nx, c->p.ny, cus) : 0;
+  // a 1D grid that fits one workgroup runs in one launch (double precision: see the namespaces' contraction)
+  const int waves = (c->p.nx + OUT_COLS - 1) / OUT_COLS;
+  c->line = c->p.dim == 1 && !c->f32 && waves <= LINE_WAVES && !std::getenv("SWE_HWENO_ROWS") ? waves : 0;
 }
 
 // The device scalars in one copy (every copy to pageable memory costs a round trip), and the error they report,
@@ -649,6 +674,11 @@ template <class T> int rhs_impl(swe_hweno_ctx* c, const T* state, T* rhs, double
   if (alpha_x > 0 && c->p.dim == 2 && !(alpha_y > 0 && std::isfinite(alpha_y))) return SWE_EINVAL;
   const size_t bytes = c->n * c->nf * sizeof(T);
   if ((const char*)rhs < (const char*)state + bytes && (const char*)state < (const char*)rhs + bytes) return SWE_EINVAL;
+  if constexpr (sizeof(T) == 8) if (c->line && !c->timing) {
+    launch_line(c, const_cast<double*>(state), rhs, 0, false, 0, 0.0, alpha_x, c->stream);
+    if (hipGetLastError() != hipSuccess) return SWE_EHIP;
+    return (c->p.flags & SWE_CHECK_DRY) ? take_device_error(c) : SWE_OK;
+  }
   if (alpha_x < 0) launch_alpha<T>(c, state, SP_RHS, false, 0.0, c->stream);
   else
     hipLaunchKernelGGL(k_set_speeds, dim3(1), dim3(ASLOTS), 0, c->stream, speeds_set(c, SP_RHS), dbits(alpha_x),
@@ -688,13 +718,22 @@ template <class T> int alpha_impl(swe_hweno_ctx* c, const T* state, double* alph
   return e;
 }
 
+// A single step and the start of its clock.
+template <class T> void launch_step(swe_hweno_ctx* c, T* state, hipStream_t s) {
+  if constexpr (sizeof(T) == 8) if (c->line && !c->timing) {
+    launch_line(c, state, nullptr, 1, true, 0, 0.0, 0.0, s);
+    return;
+  }
+  launch_alpha<T>(c, state, SP_N, true, 0.0, s);
+  enqueue_step<T>(c, state, 0, s);
+}
+
 template <class T> int step_impl(swe_hweno_ctx* c, T* state, double dt, double* dt_used) {
   if (!c || !state || !is_type<T>(c)) return SWE_EINVAL;
   if (!(dt <= DBL_MAX)) return SWE_EINVAL;
   const swe_hweno_params saved = c->p;
   if (dt > 0) { c->p.flags |= SWE_FIXED_DT; c->p.fixed_dt = dt; }
-  launch_alpha<T>(c, state, SP_N, true, 0.0, c->stream);
-  enqueue_step<T>(c, state, 0, c->stream);
+  launch_step<T>(c, state, c->stream);
   c->p = saved;
   if (hipGetLastError() != hipSuccess) return SWE_EHIP;
   if (dt_used) {
@@ -707,30 +746,38 @@ template <class T> int step_impl(swe_hweno_ctx* c, T* state, double dt, double* 
 }
 
 constexpr long GRAPH_AFTER = 256;
+constexpr int LINE_STEPS = 1024;  // steps of a launch of k_line, about 7 ms
 
 template <class T> int run_impl(swe_hweno_ctx* c, T* state, int nsteps, double t_end, double* t_out, int* steps_out) {
   if (!c || !state || !is_type<T>(c)) return SWE_EINVAL;
   if (!(t_end <= DBL_MAX) || (nsteps <= 0 && !(t_end > 0))) return SWE_EINVAL;
   const int use_tend = t_end > 0 ? 1 : 0;
-  if (c->g_state != state || c->g_tend != use_tend) {
+  bool line = false;
+  if constexpr (sizeof(T) == 8) line = c->line && !c->timing;
+  if (!line && (c->g_state != state || c->g_tend != use_tend)) {
     destroy_graphs(c);
     c->g_state = state;
     c->g_tend = use_tend;
     c->g_steps = 0;
   }
   // t = 0, t_end, steps = 0 and alpha of the initial state
-  launch_alpha<T>(c, state, SP_N, true, t_end, c->stream);
+  if (!line) launch_alpha<T>(c, state, SP_N, true, t_end, c->stream);
   if (hipGetLastError() != hipSuccess) return SWE_EHIP;
   int done = 0;
-  const int chunk = 64;
+  const int chunk = line ? LINE_STEPS : 64;
   for (;;) {
     int todo = nsteps > 0 ? nsteps - done : chunk;
     if (todo <= 0) break;
-    if (use_tend && todo > chunk) todo = chunk;
+    if ((use_tend || line) && todo > chunk) todo = chunk;
     int k = 0;
+    if constexpr (sizeof(T) == 8) if (line) {
+      launch_line(c, state, nullptr, todo, done == 0, use_tend, t_end, 0.0, c->stream);
+      if (hipGetLastError() != hipSuccess) return SWE_EHIP;
+      k = todo;
+    }
     // capturing costs what the replays of some 200 steps save (120 us; a replayed step of small kernels is
     // 2 to 4% faster than its three launches), so the first steps on a state are launched directly
-    if (c->timing || (!c->g8 && c->g_steps < GRAPH_AFTER)) {
+    if (!line && (c->timing || (!c->g8 && c->g_steps < GRAPH_AFTER))) {
       for (; k < todo && (c->timing || c->g_steps < GRAPH_AFTER); ++k) {
         enqueue_step<T>(c, state, use_tend, c->stream);
         if (!c->timing) c->g_steps += 1;
@@ -819,8 +866,7 @@ int step_noalloc_impl(const swe_hweno_params* p, double* state, const double* b,
   if (dt > 0) { c.p.flags |= SWE_FIXED_DT; c.p.fixed_dt = dt; }
   hipLaunchKernelGGL(k_setup, dim3(1), dim3(ASLOTS), 0, c.stream, c.sc, c.sp, dbits(p->alpha_x),
                      dbits(p->dim == 2 ? p->alpha_y : 0.0));
-  launch_alpha<double>(&c, state, SP_N, true, 0.0, c.stream);
-  enqueue_step<double>(&c, state, 0, c.stream);
+  launch_step<double>(&c, state, c.stream);
   if (hipGetLastError() != hipSuccess) return SWE_EHIP;
   if (dt_used) {
     DevScal s;

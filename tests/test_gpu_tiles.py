@@ -72,3 +72,55 @@ def test_small_tile_reports_dry_and_nonfinite():
             assert e.value.code in ((code,) if code == -5 else (-4, -5))
             with pytest.raises(SweError):
                 s.run(st.clone(), nsteps=2)
+
+
+@pytest.mark.parametrize("nx", [4, 5, 59, 60, 61, 120, 200, 479, 480, 481])
+@pytest.mark.parametrize("bc", [0, 1])
+def test_line_runs_give_the_bits_of_stages(nx, bc):
+    """1D grids of up to 480 nodes run in one launch: against a launch per stage, with the limiter and without, at
+    CFL and fixed steps, with frozen speeds, to a final time, and the bare right-hand side."""
+    import torch
+
+    from paper_2208_01260_amd import inputs
+    from paper_2208_01260_amd._lib import FIXED_ALPHA, FIXED_DT, NO_LIMITER
+
+    pr = inputs.c1_1d(max(nx, 4))
+    pr.bc = (bc, 0)
+    for kw in (dict(), dict(flags=NO_LIMITER), dict(flags=FIXED_DT | FIXED_ALPHA, fixed_dt=1e-5, alpha=(6.0, 0.0)),
+               dict(flags=FIXED_ALPHA, alpha=(6.0, 0.0))):
+        out = []
+        for force in (0, 16):
+            with _solver(pr, force, torch.float64, **kw) as s:
+                st = torch.from_numpy(pr.state).cuda()
+                x, y, z = st.clone(), st.clone(), st.clone()
+                t = s.run(x, nsteps=7)
+                dt = [s.step(y, sync=True), s.step(y, dt=2e-6, sync=True), s.step(y)]
+                u = s.run(z, t_end=2.5 * dt[0])
+                out.append(((s.rhs(st), s.rhs(st, alpha=(5.5, 0.0)), s.limit(st), x, y, z), t, dt, u))
+        assert all(torch.equal(a, b) for a, b in zip(out[0][0], out[1][0])), (nx, kw)
+        assert out[0][1:] == out[1][1:] and out[0][3][1] == 3, (nx, kw)
+
+
+def test_line_run_of_many_launches_and_errors():
+    import torch
+
+    from paper_2208_01260_amd import inputs
+    from paper_2208_01260_amd.solver import SweError
+
+    pr = inputs.c1_1d(40)
+    res = []
+    for force in (0, 16):
+        with _solver(pr, force, torch.float64) as s:
+            st = torch.from_numpy(pr.state).cuda()
+            res.append((st, s.run(st, nsteps=2100)))
+    assert torch.equal(res[0][0], res[1][0]) and res[0][1] == res[1][1] and res[0][1][1] == 2100
+    for bad, code in ((-5.0, -4), (float("nan"), -5)):
+        got = []
+        for force in (0, 16):
+            with _solver(pr, force, torch.float64) as s:
+                st = torch.from_numpy(pr.state).cuda()
+                st[0, 39] = bad
+                with pytest.raises(SweError) as e:
+                    s.run(st, nsteps=1)
+                got.append(e.value.code)
+        assert got[0] == got[1]
