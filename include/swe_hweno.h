@@ -238,7 +238,7 @@ int swe_hweno_batch_init(const swe_hweno_params* common, const swe_hweno_instanc
                          swe_hweno_batch** out);
 
 /* nsteps SSP-RK3 steps of every instance (each at its own CFL step; no end time), replayed from
- * captured graphs. Every run starts each instance's clock at 0 and its speeds from its current
+ * captured graphs once some 256 steps have run. Every run starts each instance's clock at 0 and its speeds from its current
  * state; t_out (HOST array of count, nullable) receives the time each instance advanced.
  * Synchronises. An instance whose time step turns non-finite, or whose state is found dry or
  * non-finite (by the speeds of its initial state or of a stage's result), stops at the start of
@@ -247,10 +247,12 @@ int swe_hweno_batch_init(const swe_hweno_params* common, const swe_hweno_instanc
  * The error is then cleared: a later run steps the instance again. nsteps < 1 is SWE_EINVAL. */
 int swe_hweno_batch_run(swe_hweno_batch* bt, int nsteps, double* t_out);
 
-/* Rows per wavefront march of the batch kernels (>= 1); swe_hweno_batch_autotune times the
+/* Rows per wavefront march of the batch kernels at most (>= 1; an instance's rows are split into marches of
+ * about equal length). A new batch takes rows by a model of the device's rounds of wavefronts over all
+ * instances' tiles. swe_hweno_batch_autotune times that choice and the
  * first two fused stage kernels of a step (limiter as configured) on the batch's own data for a
  * set of candidates (8 to 64 rows; they write only the batch's stage buffers, the states are not
- * touched), keeps the fastest and returns it. Rows per march are the tile's one free dimension:
+ * touched), keeps the fastest and returns the fastest of the candidates. Rows per march are the tile's one free dimension:
  * its width is the 60 output columns of a 64-lane wavefront. The choice is cached for the life
  * of the process per size class: the device's architecture and compute-unit count and
  * power-of-two buckets of the instance count, the total nodes and the largest instance width

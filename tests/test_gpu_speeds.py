@@ -64,3 +64,26 @@ def test_run_takes_the_steps_of_single_steps(nx, ny):
         again = torch.from_numpy(pr.state).cuda()
         t2, k2 = s.run(again, t_end=t * (1 - 1e-9))  # the last step is clipped
         assert k2 == 11 and t2 == t * (1 - 1e-9)
+
+
+def test_replayed_graphs_give_the_bits_of_direct_launches():
+    """Runs capture their graphs after 256 steps on a state: long runs, then several shorter ones with eager work in
+    between, against single steps; a batch likewise, against plain runs."""
+    import torch
+
+    from paper_2208_01260_amd import inputs
+    from paper_2208_01260_amd.solver import Batch, Solver
+
+    pr = inputs.c2_2d(61, "smooth", ny=40)
+    with Solver.from_problem(pr) as s, Solver.from_problem(pr) as ref, Batch([pr, inputs.c2_2d(16, "smooth", ny=50)]) as bt:
+        st = torch.from_numpy(pr.state).cuda()
+        one = st.clone()
+        for n in (270, 9, 17, 1, 40):
+            t, k = s.run(st, nsteps=n)
+            tb = bt.run(n)
+            tt = 0.0
+            for _ in range(n):
+                tt += ref.step(one, sync=True)
+            (one * 2.0).sum().item()  # work of the program's own between the replays
+            assert k == n and t == tt and torch.equal(st, one), n
+            assert tb[0] == t and torch.equal(bt.states[0], one), n
