@@ -516,12 +516,14 @@ template <class T> void enqueue_step(swe_hweno_ctx* c, T* state, int use_tend, h
 int hip_status(hipError_t e) { return e == hipSuccess ? SWE_OK : SWE_EHIP; }
 
 // Rows marched per wave in 2D: the wave count gx * ceil(ny / rows) should fill whole rounds of
-// the resident-wave slots (one fused-stage wave per SIMD), while each march repays its start-up
-// (four window rows and one extra y-interface, about two rows of work). Cost model: rounds *
-// (rows + 2) over 3 .. 128 rows; ties go to fewer rows. Small grids, which cannot fill the GPU,
-// get short marches and so more wavefronts; below 3 rows the start-up of each wavefront costs
-// more than the extra wavefronts gain. SWE_HWENO_ROWS overrides the choice.
-int choose_rows(int nx, int ny, int slots) {
+// the SIMDs, while each march repays its start-up (four window rows and one extra y-interface,
+// about two rows of work). Cost model: rounds * (rows + 2) over 3 .. 128 rows; ties go to fewer
+// rows. Small grids, which cannot fill the GPU, get short marches and so more wavefronts; below 3
+// rows the start-up of each wavefront costs more than the extra wavefronts gain. In double precision a SIMD holds one
+// wavefront. In single precision it holds two, whose rows take 6.1 us together against 3.9 us of one alone
+// (2048^2): a round is 2 wavefronts per SIMD at 1.54, its rest counts 1 or 1.54. (At 2048^2 36 rows, 1995 wavefronts, in
+// place of 71 rows, 1015: 292 -> 240 us a stage; the rows change no bit.) SWE_HWENO_ROWS overrides the choice.
+int choose_rows(int nx, int ny, int simds, bool two) {
   if (const char* e = std::getenv("SWE_HWENO_ROWS")) {
     const int r = std::atoi(e);
     if (r >= 1 && r <= 4096) return r;
@@ -531,8 +533,14 @@ int choose_rows(int nx, int ny, int slots) {
   double best_cost = 1e300;
   for (int r = 3; r <= 128; ++r) {
     const long waves = gx * ((ny + r - 1) / r);
-    const long rounds = (waves + slots - 1) / slots;
-    const double cost = (double)rounds * (double)(std::min(r, ny) + 2);
+    double rounds;
+    if (two) {
+      const long full = waves / (2L * simds), rest = waves % (2L * simds);
+      rounds = 1.54 * (double)full + (rest == 0 ? 0.0 : (rest <= simds ? 1.0 : 1.54));
+    } else {
+      rounds = (double)((waves + simds - 1) / simds);
+    }
+    const double cost = rounds * (double)(std::min(r, ny) + 2);
     if (cost < best_cost * (1 - 1e-12)) { best_cost = cost; best = r; }
   }
   return best;
@@ -559,7 +567,7 @@ void choose_tile(swe_hweno_ctx* c) {
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) !=
       hipSuccess || cus <= 0)
     cus = 256;
-  c->rows = choose_rows(c->p.nx, c->p.dim == 2 ? c->p.ny : 1, 4 * cus);
+  c->rows = choose_rows(c->p.nx, c->p.dim == 2 ? c->p.ny : 1, 4 * cus, c->f32 != 0);
   c->small = c->p.dim == 2 && !c->f32 ? choose_small(c->p.nx, c->p.ny, cus) : 0;
   // a 1D grid that fits one workgroup runs in one launch (double precision: see the namespaces' contraction)
   const int waves = (c->p.nx + OUT_COLS - 1) / OUT_COLS;
