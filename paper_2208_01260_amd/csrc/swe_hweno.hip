@@ -271,6 +271,7 @@ struct swe_hweno_ctx {
   const void* g_state = nullptr;
   int g_tend = 0;
   long g_steps = 0;  // steps launched on g_state before its graphs were captured
+  unsigned cus = 256;       // compute units of the device
   int rows = ROWS_DEFAULT;  // rows marched per wave (2D), chosen at init
   int small = 0;            // 2D: rows per workgroup of k_small, or 0 for marching wavefronts
   int line = 0;             // 1D: wavefronts of k_line's workgroup, or 0 for a launch per stage
@@ -567,6 +568,7 @@ void choose_tile(swe_hweno_ctx* c) {
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) !=
       hipSuccess || cus <= 0)
     cus = 256;
+  c->cus = (unsigned)cus;
   c->rows = choose_rows(c->p.nx, c->p.dim == 2 ? c->p.ny : 1, 4 * cus, c->f32 != 0);
   c->small = c->p.dim == 2 && !c->f32 ? choose_small(c->p.nx, c->p.ny, cus) : 0;
   // a 1D grid that fits one workgroup runs in one launch (double precision: see the namespaces' contraction)
