@@ -704,12 +704,24 @@ template <class T> int rhs_impl(swe_hweno_ctx* c, const T* state, T* rhs, double
 
 template <class T> int limit_impl(swe_hweno_ctx* c, const T* state, T* dmod) {
   if (!c || !state || !dmod || !is_type<T>(c)) return SWE_EINVAL;
+  if constexpr (sizeof(T) == 8) if (c->p.dim == 2) {
+    const KArgs<double> k = base_args<double>(c);
+    swe::LimitArgs<double> a{state, k.b, dmod, k.nx, k.ny, k.bcx, k.bcy, 6, k.dx, k.dy, k.idx, k.idy, k.g, k.eps};
+    while (a.lw > 2 && (1 << (a.lw - 1)) >= a.nx) --a.lw;  // 64 nodes wide, narrower where the grid is
+    const size_t w = (size_t)1 << a.lw, h = 256 >> a.lw;
+    const size_t tiles = ((size_t)a.nx + w - 1) / w * (((size_t)a.ny + h - 1) / h);
+    hipLaunchKernelGGL(swe::k_limit_tile<double>, dim3((unsigned)tiles), dim3(256), 0, c->stream, a);
+    return hip_status(hipGetLastError());
+  }
   KArgsOf<T> a = base_args<T>(c);
   a.S = state; a.out = dmod;
   const size_t blocks = (c->n + 255) / 256;
   const unsigned grid = (unsigned)(blocks < 8192 ? blocks : 8192);
-  if (c->p.dim == 2) hipLaunchKernelGGL((Kern<T>::template limit<2>), dim3(grid), dim3(256), 0, c->stream, a);
-  else hipLaunchKernelGGL((Kern<T>::template limit<1>), dim3(grid), dim3(256), 0, c->stream, a);
+  if constexpr (sizeof(T) == 4) if (c->p.dim == 2) {
+    hipLaunchKernelGGL((Kern<T>::template limit<2>), dim3(grid), dim3(256), 0, c->stream, a);
+    return hip_status(hipGetLastError());
+  }
+  hipLaunchKernelGGL((Kern<T>::template limit<1>), dim3(grid), dim3(256), 0, c->stream, a);
   return hip_status(hipGetLastError());
 }
 
