@@ -183,9 +183,11 @@ __global__ void k_reset(DevScal* s, unsigned long long* sp, double t_end) {
 
 // Threads of a workgroup of k_start.
 constexpr int START_THREADS = 1024;
-// LDS of k_small at R rows per workgroup, in numbers of the arithmetic type.
+// LDS of k_small at R rows per workgroup: the quantities and the task counter.
 constexpr int NNODE = 18;  // slots of a node's fluxes
-constexpr size_t small_lds_words(int R) { return (size_t)WAVE * (R * NNODE + (R + 1) * 14 + R * 6); }
+constexpr int SMALL_ROWS = 8;  // rows per workgroup at most
+constexpr size_t small_lds_bytes(int R, size_t esz) { return WAVE * (R * NNODE + (R + 1) * 14 + R * 6) * esz + 16; }
+static_assert(small_lds_bytes(SMALL_ROWS, sizeof(double)) <= 163840, "160 KB of LDS");
 
 }  // namespace swe
 
@@ -387,9 +389,10 @@ template <class A> void stage_speeds(const swe_hweno_ctx* c, A& a, int stage) {
 
 template <class T, int MODE> void launch_stage_mode(const swe_hweno_ctx* c, const KArgsOf<T>& a, hipStream_t s) {
   if constexpr (sizeof(T) == 8) if (c->small) {
-    const size_t lds = small_lds_words(c->small) * sizeof(T);
-    if (c->small == 1) hipLaunchKernelGGL((swe::k_small<T, MODE, 4>), stage_grid(c), dim3(4 * WAVE), lds, s, a);
-    else hipLaunchKernelGGL((swe::k_small<T, MODE, 8>), stage_grid(c), dim3(8 * WAVE), lds, s, a);
+    const size_t lds = small_lds_bytes(c->small, sizeof(T));
+    if (c->small == 1) hipLaunchKernelGGL((swe::k_small<T, MODE, 4, true>), stage_grid(c), dim3(4 * WAVE), lds, s, a);
+    else if (c->small == 2) hipLaunchKernelGGL((swe::k_small<T, MODE, 8, true>), stage_grid(c), dim3(8 * WAVE), lds, s, a);
+    else hipLaunchKernelGGL((swe::k_small<T, MODE, 8, false>), stage_grid(c), dim3(8 * WAVE), lds, s, a);
     return;
   }
   if (c->p.dim == 2) hipLaunchKernelGGL((Kern<T>::template stage<2, MODE>), stage_grid(c), dim3(WAVE), 0, s, a);
@@ -549,11 +552,10 @@ int choose_rows(int nx, int ny, int simds, bool two) {
 
 // Rows per workgroup of k_small, or 0 for marching wavefronts: the fewest for which every workgroup is resident at
 // once, one per CU, up to 8 (their LDS). With one row a workgroup has 4 wavefronts, one per SIMD, else 8. A further
-// row costs about 1.5 us, from 7.7 us at one row to 17.8 at 8; marching wavefronts take 19.3 us at their shortest marches, 22
-// where this rule ends (about 340^2), and 24 at 400^2, where two rounds of 6 rows take 28.7. Double
+// row costs about 1.5 us, from 6.8 us at one row to 17.6 at 8; marching wavefronts take 18.8 us at their shortest marches, 20.6
+// where this rule ends (about 340^2), and 21.9 at 400^2, where two rounds of 6 rows would take 28. Double
 // precision only: in single precision (6.9 to 13.3 us against 16.9) the two tilings would round differently. A choice of
 // rows by the environment keeps the marching wavefronts.
-constexpr int SMALL_ROWS = 8;
 int choose_small(int nx, int ny, int cus) {
   if (std::getenv("SWE_HWENO_ROWS")) return 0;
   const long gx = (nx + OUT_COLS - 1) / OUT_COLS;
