@@ -121,26 +121,6 @@ __device__ __forceinline__ void hweno_with_vjp(double f0, double f1, double f2, 
   s2b -= K16 * q2b;
 }
 
-// Reverse of one projected triple: y = (l1a v0 - i2c v1, v2 - ut v0, l3a v0 + i2c v1).
-__device__ __forceinline__ void proj_vjp(double l1a, double l3a, double i2c, double ut, double v0, double v1,
-                                         const double yb[3], double& v0b, double& v1b, double& v2b, double& l1ab,
-                                         double& l3ab, double& i2cb, double& utb) {
-  v0b += l1a * yb[0] - ut * yb[1] + l3a * yb[2];
-  v1b += i2c * (yb[2] - yb[0]);
-  v2b += yb[1];
-  l1ab += v0 * yb[0];
-  l3ab += v0 * yb[2];
-  i2cb += v1 * (yb[2] - yb[0]);
-  utb -= v0 * yb[1];
-}
-
-// Row f of the characteristic matrix L applied to a triple: rows (l1a, -i2c, 0), (-ut, 0, 1),
-// (l3a, i2c, 0); proj_vjp is its reverse over the three rows.
-__device__ __forceinline__ double proj_row(int f, double l1a, double l3a, double i2c, double ut, double v0, double v1,
-                                           double v2) {
-  return f == 0 ? l1a * v0 - i2c * v1 : (f == 1 ? v2 - ut * v0 : l3a * v0 + i2c * v1);
-}
-
 // Reverse of node_frame<DIR>: adds the adjoint of the raw record r (slots of hweno_device.hpp)
 // given the adjoints of the NodeF fields.
 template <int DIR>

@@ -3,14 +3,16 @@
 // derivative limiter and SSP-RK3 stages (Zhao & Zhang, arXiv 2208.01260), in FP64 or FP32 (the
 // same kernels instantiated for both types).
 //
-// Kernel design (one wavefront per workgroup):
-//   * k_stage is the whole stage of eq. (2.11) in one pass: each lane owns one grid column and
-//     marches up a strip of rows. The y-sweep keeps a four-row window of raw node records in
+// Kernel design (the kernels of the scheme are in hweno_stage.inc, included once per arithmetic type):
+//   * k_stage, one wavefront per workgroup, is the whole stage of eq. (2.11) in one pass: each lane owns one grid
+//     column and marches up a strip of rows. The y-sweep keeps a four-row window of raw node records in
 //     registers and carries the interface flux of the previous row, so each y-interface is
 //     computed once. The x-sweep exchanges the current row between lanes through LDS: lane l
 //     computes the interface left of its column and reads the right one from lane l+1. A wave
 //     covers 64 columns (2 halo columns each side) and writes the 60 interior ones.
-//   * The same kernel writes the bare right-hand side (MODE_RHS), or fuses the limiter of
+//   * k_small is the same stage for 2D grids too small to fill the GPU with marches: a workgroup shares out the interfaces
+//     and limiters of a few rows. k_line is a whole 1D run in one launch where the grid fits a workgroup.
+//   * The stage kernels write the bare right-hand side (MODE_RHS), or fuse the time step, the limiter of
 //     Sec. 2.2 at the node, the Runge-Kutta combination and the max-reduction of the next
 //     stage's Lax-Friedrichs speeds (MODE_STAGE0/1/2).
 //   * Boundary nodes are read through an index fold: periodic wrap, or the mirror about the wall
