@@ -804,8 +804,6 @@ template <class T> int run_impl(swe_hweno_ctx* c, T* state, int nsteps, double t
       if (hipGetLastError() != hipSuccess) return SWE_EHIP;
       k = todo;
     }
-    // capturing costs what the replays of some 200 steps save (120 us; a replayed step of small kernels is
-    // 2 to 4% faster than its three launches), so the first steps on a state are launched directly
     if (!line && (c->timing || (!c->g8 && c->g_steps < GRAPH_AFTER))) {
       for (; k < todo && (c->timing || c->g_steps < GRAPH_AFTER); ++k) {
         enqueue_step<T>(c, state, use_tend, c->stream);
