@@ -290,7 +290,8 @@ int swe_hweno_rhs_vjp(swe_hweno_ctx* ctx, const double* state, double alpha_x, d
                       double* sbar, double* bbar, double* bxbar, double* bybar);
 
 /* dmbar (6 planes: H1, M1, W1, H2, M2, W2) is the adjoint of Lim(state); sbar (state layout)
- * and bbar receive its products with dLim/dstate and dLim/db. */
+ * and bbar receive its products with dLim/dstate and dLim/db. sbar may be the state or lie over
+ * dmbar (as that of swe_hweno_rhs_vjp over its inputs): the result is the same. */
 int swe_hweno_limit_vjp(swe_hweno_ctx* ctx, const double* state, const double* dmbar, double* sbar, double* bbar);
 
 /* Reverse of nsteps steps of swe_hweno_run from state0 (not modified). The context must have

@@ -1,0 +1,38 @@
+"""GPU: calls at the edges of what they accept: outputs that overlap inputs, runs that meet a dry node, and work memory that
+has to grow, is refused or is short."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+# ------------------------------------------------------------------ outputs over inputs
+@pytest.mark.parametrize("nx,ny", [(16, 9), (177, 160), (250, 256), (300, 281)])  # tiles of 8, 8, 16 with and without own items
+def test_products_in_place(inputs_mod, nx, ny):
+    """The state's adjoint may take the place of the state, or of the adjoint that is multiplied, whole or in part: the bits are
+    those of a product into memory of its own."""
+    import torch
+
+    from paper_2208_01260_amd import _lib
+    from paper_2208_01260_amd.solver import Solver
+
+    L, pr, n = _lib.lib(), inputs_mod.c3_2d(nx, ny=ny), nx * ny
+    st = torch.from_numpy(pr.state).cuda().contiguous()
+    wave = torch.sin(torch.arange(9 * n, dtype=torch.float64, device="cuda"))
+    planes = [torch.empty(n, dtype=torch.float64, device="cuda") for _ in range(3)]
+    with Solver.from_problem(pr) as s:
+        want = [x.flatten() for x in s.limit_vjp(st, wave[:6 * n].reshape(6, ny, nx).contiguous())]
+        want_rhs = [x.flatten() for x in s.rhs_vjp(st, wave.reshape(9, ny, nx), (12.0, 13.0))]
+        # places of the state, of dmbar (or rbar) and of sbar in one buffer, in nodes
+        for at_s, at_d, at_o in ((0, 9 * n, 0), (0, 9 * n, 9 * n), (0, 12 * n, 9 * n), (0, 9 * n, 9 * n - n // 2 - 1),
+                                 (9 * n, 0, 5 * n + 3), (0, 9 * n, 8 * n)):
+            buf = torch.zeros(21 * n, dtype=torch.float64, device="cuda")
+            p = buf.data_ptr()
+            put = lambda m: (buf[at_s:at_s + 9 * n].copy_(st.flatten()), buf[at_d:at_d + m].copy_(wave[:m]))  # noqa: E731
+            put(6 * n)
+            assert L.swe_hweno_limit_vjp(s._ctx, p + 8 * at_s, p + 8 * at_d, p + 8 * at_o, planes[0].data_ptr()) == 0
+            assert torch.equal(buf[at_o:at_o + 9 * n], want[0]) and torch.equal(planes[0], want[1]), (at_s, at_d, at_o)
+            put(9 * n)
+            assert L.swe_hweno_rhs_vjp(s._ctx, p + 8 * at_s, 12.0, 13.0, p + 8 * at_d, p + 8 * at_o,
+                                       *[x.data_ptr() for x in planes]) == 0
+            assert torch.equal(buf[at_o:at_o + 9 * n], want_rhs[0])
+            assert all(torch.equal(a, b) for a, b in zip(planes, want_rhs[1:]))
