@@ -249,10 +249,10 @@ int swe_hweno_batch_run(swe_hweno_batch* bt, int nsteps, double* t_out);
 
 /* Rows per wavefront march of the batch kernels at most (>= 1; an instance's rows are split into marches of
  * about equal length). A new batch takes rows by a model of the device's rounds of wavefronts over all
- * instances' tiles. swe_hweno_batch_autotune times that choice and the
+ * instances' tiles. swe_hweno_batch_autotune takes timed rows in its place: it times the
  * first two fused stage kernels of a step (limiter as configured) on the batch's own data for a
  * set of candidates (8 to 64 rows; they write only the batch's stage buffers, the states are not
- * touched), keeps the fastest and returns the fastest of the candidates. Rows per march are the tile's one free dimension:
+ * touched), keeps the fastest and returns it. Rows per march are the tile's one free dimension:
  * its width is the 60 output columns of a 64-lane wavefront. The choice is cached for the life
  * of the process per size class: the device's architecture and compute-unit count and
  * power-of-two buckets of the instance count, the total nodes and the largest instance width
