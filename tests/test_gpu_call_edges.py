@@ -36,3 +36,27 @@ def test_products_in_place(inputs_mod, nx, ny):
                                        *[x.data_ptr() for x in planes]) == 0
             assert torch.equal(buf[at_o:at_o + 9 * n], want_rhs[0])
             assert all(torch.equal(a, b) for a, b in zip(planes, want_rhs[1:]))
+
+
+# ------------------------------------------------------------------ long runs of a batch
+def test_batch_run_longer_than_its_direct_steps(inputs_mod):
+    """A run that goes over from launches to graphs within the call has the bits of the same steps in parts, and of the plain
+    solver, and so has one that replays from its start."""
+    import torch
+
+    from paper_2208_01260_amd.solver import Batch, Solver
+
+    probs = [inputs_mod.c2_2d(n, "smooth", ny=m) for n, m in ((23, 17), (64, 9), (31, 40))]
+    with Batch(probs) as once, Batch(probs) as parts:
+        for n in (300, 21):
+            t = once.run(n)
+            for k in (n // 3, n // 3, n - 2 * (n // 3)):
+                parts.run(k)
+            for i, pr in enumerate(probs):
+                assert torch.equal(once.states[i], parts.states[i]), (n, i)
+        for i, pr in enumerate(probs):
+            st = torch.from_numpy(pr.state).cuda().contiguous()
+            with Solver.from_problem(pr) as s:
+                s.run(st, 300)
+                assert s.run(st, 21)[0] == t[i]
+            assert torch.equal(once.states[i], st), i

@@ -38,3 +38,15 @@ def test_autotune_returns_the_rows_in_use(scenario, nx, ny, count, fast):
     assert waves == expected
     away = lambda r: max(ny / -(-ny // r) / fast, fast / (ny / -(-ny // r)))  # noqa: E731
     assert rows in (8, 12, 16, 24, 32, 48, 64) and away(rows) == min(away(r) for r in (8, 12, 16, 24, 32, 48, 64))
+
+
+@pytest.mark.parametrize("lengths", [(300,), (10000,), (255, 1, 1), (200, 200), (1, 256, 17), (256, 5)])
+def test_batch_replays_graphs_after_256_steps(scenario, lengths):
+    """Every step is launched once (three stages); the first 256 directly, within a call or over several, the rest by replays of
+    16 steps and one of the remainder."""
+    left = 256
+    for n, (direct, graphs, replayed) in zip(lengths, scenario("batch", *lengths)):
+        by_hand = min(left, n)
+        left -= by_hand
+        assert direct == 3 * by_hand and replayed == 3 * (n - by_hand)
+        assert graphs == -(-(n - by_hand) // 16)
