@@ -306,7 +306,9 @@ int swe_hweno_run_vjp(swe_hweno_ctx* ctx, const double* state0, int nsteps, int 
 /* The same reverse in two halves, for callers that run the forward themselves (an autograd
  * forward): swe_hweno_run_checkpointed advances state in place by nsteps steps (as
  * swe_hweno_run; same flags required) and keeps the states at the start of every
- * checkpoint_every steps in the context; swe_hweno_run_vjp_checkpointed then runs the reverse
+ * checkpoint_every steps in the context. A dry or non-finite node ends the run after the segment of
+ * checkpoint_every steps that met it, whose state is left; its error is returned and no checkpoints are kept.
+ * swe_hweno_run_vjp_checkpointed then runs the reverse
  * of that run from those checkpoints (nsteps and checkpoint_every must match, else SWE_EINVAL;
  * a swe_hweno_run_vjp call on the context in between discards them). Outputs as for
  * swe_hweno_run_vjp. */
