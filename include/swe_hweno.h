@@ -321,7 +321,8 @@ int swe_hweno_run_vjp_checkpointed(swe_hweno_ctx* ctx, int nsteps, int checkpoin
  * stream first and discards saved checkpoints) or swe_hweno_destroy has returned, and is not freed by
  * the library. swe_hweno_adjoint_bytes is what a run of nsteps steps with that checkpoint interval needs (nsteps
  * = 0: the right-hand side's and the limiter's products); 0 for a context or arguments that have no
- * adjoint. A later call that needs more returns SWE_ENOMEM. */
+ * adjoint. A later call that needs more returns SWE_ENOMEM. With mem null and bytes 0 the memory goes
+ * back, the caller's to the caller, and the library allocates again where it needs to. */
 unsigned long swe_hweno_adjoint_bytes(const swe_hweno_ctx* ctx, int nsteps, int checkpoint_every);
 int swe_hweno_adjoint_memory(swe_hweno_ctx* ctx, void* mem, unsigned long bytes);
 

@@ -152,9 +152,17 @@ class Solver:
         need = self._L.swe_hweno_adjoint_bytes(self._ctx, int(nsteps), int(checkpoint_every))
         if need and (self._adj is None or self._adj.numel() < need):
             mem = self._block(need)
+            if mem is None and self._adj is not None:  # no room beside the smaller block, which goes first
+                self._set_adjoint_memory(None)
+                mem = self._block(need)
             if mem is not None:
-                _lib.check(self._L.swe_hweno_adjoint_memory(self._ctx, mem.data_ptr(), need), "swe_hweno_adjoint_memory")
-                self._adj = mem
+                self._set_adjoint_memory(mem)
+
+    def _set_adjoint_memory(self, mem):
+        """The adjoint's block, or None: the library then allocates where it needs to."""
+        ptr, n = (None, 0) if mem is None else (mem.data_ptr(), mem.numel())
+        _lib.check(self._L.swe_hweno_adjoint_memory(self._ctx, ptr, n), "swe_hweno_adjoint_memory")
+        self._adj = mem
 
     def rhs_vjp(self, state, rbar, alpha):
         """(sbar, bbar, bxbar, bybar) = rbar^T d R(state) / d(state, b, bx, by), alpha frozen."""

@@ -119,3 +119,35 @@ def test_checkpointed_run_stops_after_the_segment_in_error(inputs_mod, dry_first
             t.run_checkpointed(st, 2, 1)
         t.run_checkpointed(u, 2, 1)
     assert torch.equal(u, v)
+
+
+# ------------------------------------------------------------------ work memory
+def room(nbytes):
+    """Leaves torch's allocator room for nbytes beyond what it holds (the device itself has more); None: all of it."""
+    import torch
+
+    torch.cuda.empty_cache()
+    total = torch.cuda.get_device_properties(0).total_memory
+    torch.cuda.set_per_process_memory_fraction(
+        1.0 if nbytes is None else (torch.cuda.memory_reserved() + nbytes) / total)
+
+
+def test_adjoint_memory_grows_where_torch_has_no_room(inputs_mod):
+    """A longer run after a single product, with room for the outputs alone: the library allocates for itself."""
+    import torch
+
+    pr = inputs_mod.c3_2d(200, ny=160)
+    s, st = fixed(pr, dt=1e-5)
+    seed = torch.sin(torch.arange(st.numel(), dtype=torch.float64, device="cuda")).reshape(st.shape)
+    want = s.run_vjp(st, 12, seed, 12)
+    s.close()
+    s, _ = fixed(pr, dt=1e-5)
+    one = s.rhs_vjp(st, seed, (12.0, 12.0))
+    try:
+        room(40 << 20)  # the run's block has 27 planes of 0.25 MB per step
+        got = s.run_vjp(st, 12, seed, 12)
+        again = s.rhs_vjp(st, seed, (12.0, 12.0))
+    finally:
+        room(None)
+    s.close()
+    assert all(torch.equal(a, b) for a, b in zip(got, want)) and all(torch.equal(a, b) for a, b in zip(again, one))
