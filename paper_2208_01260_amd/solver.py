@@ -37,7 +37,7 @@ class Solver:
         self.dtype = dtype
         sfx = "_f32" if dtype == torch.float32 else ""
         self._fn = {k: getattr(L, f"swe_hweno_{k}{sfx}") for k in ("init", "rhs", "limit", "alpha", "step", "run")}
-        self._adj = None
+        self._adj, self._adj_bytes = None, 0
         self.dim, self.nx, self.ny = dim, nx, (ny if dim == 2 else 1)
         self.nf = 9 if dim == 2 else 4
         self.shape = (9, self.ny, nx) if dim == 2 else (4, nx)
@@ -148,15 +148,25 @@ class Solver:
         return torch.empty((self.ny, self.nx), dtype=torch.float64, device="cuda") if like is None else like
 
     def _adjoint_memory(self, nsteps=0, checkpoint_every=1):
-        """Work memory of the adjoint for a run (or a single product), before the call that needs it."""
+        """Work memory of the adjoint for a run (or a single product), before the call that needs it. What there is stays
+        while it is enough, the library's own too: it may hold checkpoints."""
+        if nsteps == 0 and self._adj_bytes:  # a single product needs no more than any run
+            return
         need = self._L.swe_hweno_adjoint_bytes(self._ctx, int(nsteps), int(checkpoint_every))
-        if need and (self._adj is None or self._adj.numel() < need):
+        if need <= self._adj_bytes:
+            return
+        mem = self._block(need)
+        if mem is None and self._adj is not None:  # no room beside the smaller block, which goes first
+            self._set_adjoint_memory(None)
             mem = self._block(need)
-            if mem is None and self._adj is not None:  # no room beside the smaller block, which goes first
-                self._set_adjoint_memory(None)
-                mem = self._block(need)
-            if mem is not None:
-                self._set_adjoint_memory(mem)
+        if mem is not None:
+            self._set_adjoint_memory(mem)
+        self._adj_bytes = need
+
+    def _adjoint_check(self, rc, where):
+        if rc == _lib.ENOMEM:  # the library has let go of what it had
+            self._adj_bytes = 0 if self._adj is None else self._adj.numel()
+        _lib.check(rc, where)
 
     def _set_adjoint_memory(self, mem):
         """The adjoint's block, or None: the library then allocates where it needs to."""
@@ -169,9 +179,9 @@ class Solver:
         self._adjoint_memory()
         sbar = torch.empty_like(state)
         bb, bxb, byb = self._planes(), self._planes(), self._planes()
-        _lib.check(self._L.swe_hweno_rhs_vjp(self._ctx, self._state(state), float(alpha[0]), float(alpha[1]),
-                                             self._state(rbar, "rbar"), sbar.data_ptr(), bb.data_ptr(),
-                                             bxb.data_ptr(), byb.data_ptr()), "swe_hweno_rhs_vjp")
+        self._adjoint_check(self._L.swe_hweno_rhs_vjp(self._ctx, self._state(state), float(alpha[0]), float(alpha[1]),
+                                                      self._state(rbar, "rbar"), sbar.data_ptr(), bb.data_ptr(),
+                                                      bxb.data_ptr(), byb.data_ptr()), "swe_hweno_rhs_vjp")
         return sbar, bb, bxb, byb
 
     def limit_vjp(self, state, dmbar):
@@ -180,17 +190,17 @@ class Solver:
         sbar = torch.empty_like(state)
         bb = self._planes()
         dshape = (6, self.ny, self.nx)
-        _lib.check(self._L.swe_hweno_limit_vjp(self._ctx, self._state(state), _dev(dmbar, "dmbar", shape=dshape),
-                                               sbar.data_ptr(),
-                                               bb.data_ptr()), "swe_hweno_limit_vjp")
+        self._adjoint_check(self._L.swe_hweno_limit_vjp(self._ctx, self._state(state),
+                                                        _dev(dmbar, "dmbar", shape=dshape), sbar.data_ptr(),
+                                                        bb.data_ptr()), "swe_hweno_limit_vjp")
         return sbar, bb
 
     def run_checkpointed(self, state, nsteps, checkpoint_every=10):
         """nsteps fixed-dt, frozen-alpha steps of state in place, keeping checkpoints for
         run_vjp_checkpointed."""
         self._adjoint_memory(nsteps, checkpoint_every)
-        _lib.check(self._L.swe_hweno_run_checkpointed(self._ctx, self._state(state), int(nsteps),
-                                                      int(checkpoint_every)), "swe_hweno_run_checkpointed")
+        self._adjoint_check(self._L.swe_hweno_run_checkpointed(self._ctx, self._state(state), int(nsteps),
+                                                               int(checkpoint_every)), "swe_hweno_run_checkpointed")
 
     def run_vjp_checkpointed(self, nsteps, sbar_T, checkpoint_every=10):
         """Reverse of the last run_checkpointed: (sbar_0, bbar, bxbar, bybar)."""
@@ -208,9 +218,10 @@ class Solver:
         self._adjoint_memory(nsteps, checkpoint_every)
         sbar0 = torch.empty_like(state0)
         bb, bxb, byb = self._planes(), self._planes(), self._planes()
-        _lib.check(self._L.swe_hweno_run_vjp(self._ctx, self._state(state0), int(nsteps), int(checkpoint_every),
-                                             self._state(sbar_T, "sbar_T"), sbar0.data_ptr(), bb.data_ptr(),
-                                             bxb.data_ptr(), byb.data_ptr()), "swe_hweno_run_vjp")
+        self._adjoint_check(self._L.swe_hweno_run_vjp(self._ctx, self._state(state0), int(nsteps),
+                                                      int(checkpoint_every), self._state(sbar_T, "sbar_T"),
+                                                      sbar0.data_ptr(), bb.data_ptr(), bxb.data_ptr(), byb.data_ptr()),
+                            "swe_hweno_run_vjp")
         return sbar0, bb, bxb, byb
 
     def close(self):

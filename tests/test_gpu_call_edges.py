@@ -151,3 +151,27 @@ def test_adjoint_memory_grows_where_torch_has_no_room(inputs_mod):
         room(None)
     s.close()
     assert all(torch.equal(a, b) for a, b in zip(got, want)) and all(torch.equal(a, b) for a, b in zip(again, one))
+
+
+def test_single_products_keep_checkpoints_in_the_librarys_memory(inputs_mod):
+    """A checkpointed run that torch had no room for: products between its halves leave the checkpoints where they are."""
+    import torch
+
+    pr = inputs_mod.c3_2d(200, ny=160)
+    s, st = fixed(pr, dt=1e-5)
+    seed = torch.sin(torch.arange(st.numel(), dtype=torch.float64, device="cuda")).reshape(st.shape)
+    want = s.run_vjp(st, 12, seed, 12)
+    s.close()
+    s, _ = fixed(pr, dt=1e-5)
+    x = st.clone()
+    try:
+        room(40 << 20)
+        s.run_checkpointed(x, 12, 12)
+    finally:
+        room(None)
+    assert s._adj is None  # the library's own
+    s.rhs_vjp(st, seed, (12.0, 12.0))
+    s.limit_vjp(st, seed[:6].contiguous())
+    got = s.run_vjp_checkpointed(12, seed, 12)
+    s.close()
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
