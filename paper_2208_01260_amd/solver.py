@@ -148,8 +148,9 @@ class Solver:
         return torch.empty((self.ny, self.nx), dtype=torch.float64, device="cuda") if like is None else like
 
     def _adjoint_memory(self, nsteps=0, checkpoint_every=1):
-        """Work memory of the adjoint for a run (or a single product), before the call that needs it. What there is stays
-        while it is enough, the library's own too: it may hold checkpoints."""
+        """Work memory of the adjoint for a run (or a single product), before the call that needs it and after its
+        arguments were looked at. What there is stays while it is enough, the library's own too: it may hold
+        checkpoints."""
         if nsteps == 0 and self._adj_bytes:  # a single product needs no more than any run
             return
         need = self._L.swe_hweno_adjoint_bytes(self._ctx, int(nsteps), int(checkpoint_every))
@@ -176,31 +177,31 @@ class Solver:
 
     def rhs_vjp(self, state, rbar, alpha):
         """(sbar, bbar, bxbar, bybar) = rbar^T d R(state) / d(state, b, bx, by), alpha frozen."""
+        args = self._state(state), float(alpha[0]), float(alpha[1]), self._state(rbar, "rbar")
         self._adjoint_memory()
         sbar = torch.empty_like(state)
         bb, bxb, byb = self._planes(), self._planes(), self._planes()
-        self._adjoint_check(self._L.swe_hweno_rhs_vjp(self._ctx, self._state(state), float(alpha[0]), float(alpha[1]),
-                                                      self._state(rbar, "rbar"), sbar.data_ptr(), bb.data_ptr(),
-                                                      bxb.data_ptr(), byb.data_ptr()), "swe_hweno_rhs_vjp")
+        self._adjoint_check(self._L.swe_hweno_rhs_vjp(self._ctx, *args, sbar.data_ptr(), bb.data_ptr(), bxb.data_ptr(),
+                                                      byb.data_ptr()), "swe_hweno_rhs_vjp")
         return sbar, bb, bxb, byb
 
     def limit_vjp(self, state, dmbar):
         """(sbar, bbar) = dmbar^T d Lim(state) / d(state, b)."""
+        args = self._state(state), _dev(dmbar, "dmbar", shape=(6, self.ny, self.nx))
         self._adjoint_memory()
         sbar = torch.empty_like(state)
         bb = self._planes()
-        dshape = (6, self.ny, self.nx)
-        self._adjoint_check(self._L.swe_hweno_limit_vjp(self._ctx, self._state(state),
-                                                        _dev(dmbar, "dmbar", shape=dshape), sbar.data_ptr(),
-                                                        bb.data_ptr()), "swe_hweno_limit_vjp")
+        self._adjoint_check(self._L.swe_hweno_limit_vjp(self._ctx, *args, sbar.data_ptr(), bb.data_ptr()),
+                            "swe_hweno_limit_vjp")
         return sbar, bb
 
     def run_checkpointed(self, state, nsteps, checkpoint_every=10):
         """nsteps fixed-dt, frozen-alpha steps of state in place, keeping checkpoints for
         run_vjp_checkpointed."""
+        ptr = self._state(state)
         self._adjoint_memory(nsteps, checkpoint_every)
-        self._adjoint_check(self._L.swe_hweno_run_checkpointed(self._ctx, self._state(state), int(nsteps),
-                                                               int(checkpoint_every)), "swe_hweno_run_checkpointed")
+        self._adjoint_check(self._L.swe_hweno_run_checkpointed(self._ctx, ptr, int(nsteps), int(checkpoint_every)),
+                            "swe_hweno_run_checkpointed")
 
     def run_vjp_checkpointed(self, nsteps, sbar_T, checkpoint_every=10):
         """Reverse of the last run_checkpointed: (sbar_0, bbar, bxbar, bybar)."""
@@ -215,13 +216,12 @@ class Solver:
     def run_vjp(self, state0, nsteps, sbar_T, checkpoint_every=10):
         """Reverse of `nsteps` fixed-dt, frozen-alpha steps from state0: returns
         (sbar_0, bbar, bxbar, bybar) for the adjoint sbar_T of the final state."""
+        args = self._state(state0), int(nsteps), int(checkpoint_every), self._state(sbar_T, "sbar_T")
         self._adjoint_memory(nsteps, checkpoint_every)
         sbar0 = torch.empty_like(state0)
         bb, bxb, byb = self._planes(), self._planes(), self._planes()
-        self._adjoint_check(self._L.swe_hweno_run_vjp(self._ctx, self._state(state0), int(nsteps),
-                                                      int(checkpoint_every), self._state(sbar_T, "sbar_T"),
-                                                      sbar0.data_ptr(), bb.data_ptr(), bxb.data_ptr(), byb.data_ptr()),
-                            "swe_hweno_run_vjp")
+        self._adjoint_check(self._L.swe_hweno_run_vjp(self._ctx, *args, sbar0.data_ptr(), bb.data_ptr(), bxb.data_ptr(),
+                                                      byb.data_ptr()), "swe_hweno_run_vjp")
         return sbar0, bb, bxb, byb
 
     def close(self):

@@ -1,5 +1,7 @@
 """GPU: calls at the edges of what they accept: outputs that overlap inputs, runs that meet a dry node, and work memory that
 has to grow, is refused or is short."""
+import gc
+
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -175,3 +177,35 @@ def test_single_products_keep_checkpoints_in_the_librarys_memory(inputs_mod):
     got = s.run_vjp_checkpointed(12, seed, 12)
     s.close()
     assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+def test_refused_calls_keep_checkpoints_and_take_no_memory(inputs_mod):
+    import torch
+
+    from paper_2208_01260_amd.solver import Solver, SweError
+
+    pr = inputs_mod.c3_2d(64, ny=50)
+    s, st = fixed(pr, dt=1e-5)
+    seed = torch.ones_like(st)
+    want = s.run_vjp(st, 4, seed, 2)
+    s.run_checkpointed(st.clone(), 4, 2)
+    gc.collect()
+    held = torch.cuda.memory_allocated()
+    with pytest.raises(ValueError):
+        s.run_vjp(st, 60, seed[:, 1:].contiguous(), 30)
+    with pytest.raises(ValueError):
+        s.run_checkpointed(st[:, 1:].contiguous(), 60, 30)
+    with pytest.raises(SweError):
+        s.run_vjp(st, 60, seed, 0)
+    gc.collect()
+    assert torch.cuda.memory_allocated() <= held
+    got = s.run_vjp_checkpointed(4, seed, 2)
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
+    s.close()
+    with Solver.from_problem(pr) as s:  # neither a fixed step nor frozen speeds: no reverse of a run
+        gc.collect()
+        held = torch.cuda.memory_allocated()
+        with pytest.raises(SweError):
+            s.run_vjp(st, 60, seed, 30)
+        gc.collect()
+        assert torch.cuda.memory_allocated() <= held
