@@ -259,6 +259,12 @@ class Batch:
         if not problems:
             raise ValueError("a batch needs at least one instance")
         g, cfl, eps = problems[0].g, problems[0].cfl, problems[0].eps
+        # the library allocates 27 planes per instance beside torch's bottoms (3) and states (9): where the device has
+        # less, what torch's allocator keeps unused (a closed solver's blocks, say) goes back to it first, while none
+        # of it is in use again
+        need = sum(pr.nx * pr.ny for pr in problems) * 8 * (30 if states is not None else 39)
+        if torch.cuda.mem_get_info()[0] < need + (64 << 20):
+            torch.cuda.empty_cache()
         t = lambda a: torch.from_numpy(a).to(device=device, dtype=torch.float64).contiguous()
         self.states = list(states) if states is not None else [t(pr.state) for pr in problems]
         arr = (_lib.Instance * len(problems))()

@@ -209,3 +209,25 @@ def test_refused_calls_keep_checkpoints_and_take_no_memory(inputs_mod):
             s.run_vjp(st, 60, seed, 30)
         gc.collect()
         assert torch.cuda.memory_allocated() <= held
+
+
+def test_batch_takes_what_torch_holds_unused(inputs_mod, monkeypatch):
+    """Memory that torch's allocator keeps after a solver was closed is the device's again where a batch needs it."""
+    import torch
+
+    from paper_2208_01260_amd.solver import Batch, Solver
+
+    torch.cuda.empty_cache()
+    pr = inputs_mod.c3_2d(1024, ny=900)
+    Solver.from_problem(pr).close()
+    kept = torch.cuda.memory_reserved() - torch.cuda.memory_allocated()
+    assert kept > 27 * 1024 * 900 * 8
+    small = [inputs_mod.c2_2d(61, "smooth", ny=47)] * 3
+    with Batch(small) as bt:  # enough free: torch keeps its blocks
+        bt.run(1)
+    assert torch.cuda.memory_reserved() - torch.cuda.memory_allocated() >= kept // 2
+    total = torch.cuda.mem_get_info()[1]
+    monkeypatch.setattr(torch.cuda, "mem_get_info", lambda *a: (1 << 20, total))
+    with Batch(small) as bt:
+        bt.run(1)
+        assert torch.cuda.memory_reserved() - torch.cuda.memory_allocated() < kept // 2
