@@ -73,6 +73,8 @@ class Solver:
         if nbytes == 0 or not isinstance(self.stream, torch.cuda.Stream):
             return None
         try:
+            if self.stream == torch.cuda.current_stream():  # a change of streams takes 5 us
+                return torch.empty(nbytes, dtype=torch.uint8, device="cuda")
             with torch.cuda.stream(self.stream):
                 return torch.empty(nbytes, dtype=torch.uint8, device="cuda")
         except torch.cuda.OutOfMemoryError:

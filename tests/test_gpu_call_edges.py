@@ -231,3 +231,27 @@ def test_batch_takes_what_torch_holds_unused(inputs_mod, monkeypatch):
     with Batch(small) as bt:
         bt.run(1)
         assert torch.cuda.memory_reserved() - torch.cuda.memory_allocated() < kept // 2
+
+
+def test_solver_on_another_stream_than_the_current_one(inputs_mod):
+    """Blocks and results of a solver made for another stream, and of one made and used under it."""
+    import torch
+
+    from paper_2208_01260_amd.solver import FIXED_ALPHA, FIXED_DT, Solver
+
+    pr = inputs_mod.c3_2d(90, ny=71)
+    kw = dict(flags=FIXED_DT | FIXED_ALPHA, fixed_dt=1e-5, alpha=(12.0, 12.0))
+    st = torch.from_numpy(pr.state).cuda()
+    seed = torch.ones_like(st)
+    with Solver.from_problem(pr, **kw) as s:
+        want = s.run_vjp(st, 5, seed, 2)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    s = Solver.from_problem(pr, stream=side, **kw)  # made and used with another stream as the current one
+    got = s.run_vjp(st, 5, seed, 2)
+    s.close()
+    with torch.cuda.stream(side), Solver.from_problem(pr, **kw) as s:
+        under = s.run_vjp(st, 5, seed, 2)
+    torch.cuda.synchronize()
+    for other in (got, under):
+        assert all(torch.equal(a, b) for a, b in zip(other, want))
