@@ -120,8 +120,8 @@ int swe_hweno_alpha(swe_hweno_ctx* ctx, const double* state, double* alpha_host)
 int swe_hweno_step(swe_hweno_ctx* ctx, double* state, double dt, double* dt_used);
 
 /* nsteps SSP-RK3 steps (eq. (2.11) of Sec. 2.2, each as swe_hweno_step) of state in place,
- * replaying a captured per-step HIP graph after the first 256 steps on one state array. With t_end > 0 it stops at t_end (the last step
- * clipped to it; nsteps <= 0 means "until t_end"); t_out and steps_out (HOST, nullable) receive
+ * replaying a captured per-step HIP graph after the first 256 steps on one state array (a 1D grid of up to
+ * 480 nodes in FP64 runs many steps per launch instead). With t_end > 0 it stops at t_end (the last step clipped to it; nsteps <= 0 means "until t_end"); t_out and steps_out (HOST, nullable) receive
  * the time reached and the steps taken. Synchronises and returns device-detected errors. */
 int swe_hweno_run(swe_hweno_ctx* ctx, double* state, int nsteps, double t_end, double* t_out, int* steps_out);
 
@@ -238,8 +238,8 @@ int swe_hweno_batch_init(const swe_hweno_params* common, const swe_hweno_instanc
                          swe_hweno_batch** out);
 
 /* nsteps SSP-RK3 steps of every instance (each at its own CFL step; no end time), replayed from
- * captured graphs once some 256 steps have run. Every run starts each instance's clock at 0 and its speeds from its current
- * state; t_out (HOST array of count, nullable) receives the time each instance advanced.
+ * captured graphs after the batch's first 256 steps. Every run starts each instance's clock at 0 and
+ * its speeds from its current state; t_out (HOST array of count, nullable) receives the time each instance advanced.
  * Synchronises. An instance whose time step turns non-finite, or whose state is found dry or
  * non-finite (by the speeds of its initial state or of a stage's result), stops at the start of
  * the next step while the others go on: its state stays that of the step in which the error was
@@ -278,9 +278,12 @@ void swe_hweno_batch_destroy(swe_hweno_batch* bt);
  * The bottom b and its slopes bx, by enter as independent inputs; swe_hweno_bottom_slopes and
  * its transpose tie them together when the gradient with respect to b alone is wanted. Work
  * buffers are allocated on first use and kept with the context until swe_hweno_destroy: about
- * 85 planes of nx*ny doubles, plus 27 per step of the checkpoint interval (the recomputed stage
- * states of one segment) and 9 per checkpoint (or they are the caller's, swe_hweno_adjoint_memory). All arrays are DEVICE arrays; outputs are
- * overwritten. FP64 contexts only (an FP32 context returns SWE_EINVAL).
+ * 80 planes of nx*ny doubles, plus 27 per step of the checkpoint interval (the recomputed stage
+ * states of one segment) and 9 per checkpoint (or they are the caller's, swe_hweno_adjoint_memory). All
+ * arrays are DEVICE arrays; outputs are overwritten. FP64 contexts only (an FP32 context returns SWE_EINVAL).
+ * Results repeat to the bit, whatever the checkpoint interval. The interface reverse adds its three fields in
+ * one of two ways, by the grid and the device's number of compute units (one way up to two patches of 64
+ * positions per unit): the last bits of a product may differ between devices with other numbers of them.
  * ------------------------------------------------------------------------------------------ */
 
 /* rbar (state layout) is the adjoint of R(state) with alpha = (alpha_x, alpha_y) > 0 fixed.

@@ -775,7 +775,7 @@ template <class T> int step_impl(swe_hweno_ctx* c, T* state, double dt, double* 
 // replayed step is at most 1 us shorter than three launches (61 x 47 20.5 us against 20.9, 256^2 41.9 against 42 to 44) but leaves
 // the host idle: short runs go without.
 constexpr long GRAPH_AFTER = 256;
-constexpr int LINE_STEPS = 1024;  // steps of a launch of k_line, about 7 ms
+constexpr int LINE_STEPS = 1024;  // steps of a launch of k_line, about 6 ms
 
 template <class T> int run_impl(swe_hweno_ctx* c, T* state, int nsteps, double t_end, double* t_out, int* steps_out) {
   if (!c || !state || !is_type<T>(c)) return SWE_EINVAL;
